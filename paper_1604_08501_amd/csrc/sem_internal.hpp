@@ -91,6 +91,23 @@ template <typename T>
 hipError_t launch_volume_surface(int nq, const semk::BlockPtrs<T>& B, const int32_t* nbr,
                                  const semk::Phys& ph, int accumulate, hipStream_t s);
 
+// FP64 at Nq = 8 on wave-private slices (slice_f64.hip): the volume term of nf
+// fields over dirs (per_element_geo: five fields, r+s+t, metric terms per
+// element), and v + s.  The only tile of the calls that name no tile shape:
+// it measured faster than the shapes of SEM_VARIANTS from 1 element to 32768.
+template <typename T>
+constexpr bool use_slice(int nq)
+{
+    return sizeof(T) == 8 && nq == 8;
+}
+template <typename T>
+hipError_t launch_volume_slice(int nf, int dirs, bool per_element_geo,
+                               const semk::BlockPtrs<T>& B, const semk::Phys& ph, int accumulate,
+                               hipStream_t s);
+template <typename T>
+hipError_t launch_rhs_slice(const semk::BlockPtrs<T>& B, const int32_t* nbr, const semk::Phys& ph,
+                            int accumulate, hipStream_t s);
+
 // Workgroup cap of the strided k-slice and t-column launches set by
 // sem_set_max_workgroups (0 = none); one relaxed atomic load.
 int64_t max_workgroups_cap();
