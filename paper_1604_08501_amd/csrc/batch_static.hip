@@ -103,18 +103,11 @@ sem_status run(const sem_block* blocks, int32_t nblocks, const sem_phys* phys, h
 {
     using semapi::fail;
     const sem_dtype dt = sizeof(T) == 8 ? SEM_F64 : SEM_F32;
-    // built-in shapes: the smallest workgroup size for which every order has one
-    int nt = 0;
-    int epb[kMaxBlocks], lay[kMaxBlocks];
-    for (int cand : semh::kBatchThreads) {
-        bool all = true;
-        for (int i = 0; i < nblocks && all; ++i)
-            all = semapi::batch_default_shape(dt, cand, blocks[i].Nq, &epb[i], &lay[i]);
-        if (all) {
-            nt = cand;
-            break;
-        }
-    }
+    semapi::BatchOrder orders[kMaxBlocks];
+    for (int i = 0; i < nblocks; ++i)
+        orders[i] = {blocks[i].Nq, blocks[i].Ne};
+    semapi::DefaultTile shapes[kMaxBlocks];
+    const int nt = semapi::batch_default_shapes(dt, false, orders, nblocks, shapes);
     if (!nt)
         return fail(SEM_ERR_UNSUPPORTED, "no built-in batch shape covers every order of the call");
     // tile order: blocks by decreasing cost per tile (nodes per tile), ties in
@@ -122,7 +115,7 @@ sem_status run(const sem_block* blocks, int32_t nblocks, const sem_phys* phys, h
     int order[kMaxBlocks];
     for (int i = 0; i < nblocks; ++i)
         order[i] = i;
-    auto cost = [&](int i) { return (double)blocks[i].Nq * blocks[i].Nq * blocks[i].Nq * epb[i]; };
+    auto cost = [&](int i) { return (double)blocks[i].Nq * blocks[i].Nq * blocks[i].Nq * shapes[i].epb; };
     std::stable_sort(order, order + nblocks, [&](int x, int y) { return cost(x) > cost(y); });
     FillArgs<T> a{};
     a.nblocks = nblocks;
@@ -134,10 +127,10 @@ sem_status run(const sem_block* blocks, int32_t nblocks, const sem_phys* phys, h
         a.blocks[k] = semk::BatchBlock<T>{
             semapi::block_ptrs<T>(b.Ne, b.D, b.geo, b.q, b.rho_ref, b.theta_ref, b.rhs), ph,
             semk::RkStage{0.0, 0.0, 0.0}};
-        a.variant[k] = semh::variant_index(b.Nq, epb[order[k]], lay[order[k]]);
-        a.epb[k] = epb[order[k]];
-        a.first_tile[k + 1] = a.first_tile[k] + (b.Ne + epb[order[k]] - 1) / epb[order[k]];
-        lds = std::max(lds, semh::batch_lds_bytes<T>(nt, b.Nq, epb[order[k]], lay[order[k]]));
+        a.variant[k] = semh::variant_index(b.Nq, shapes[order[k]].epb, shapes[order[k]].lay);
+        a.epb[k] = shapes[order[k]].epb;
+        a.first_tile[k + 1] = a.first_tile[k] + (b.Ne + shapes[order[k]].epb - 1) / shapes[order[k]].epb;
+        lds = std::max(lds, semh::batch_lds_bytes<T>(nt, b.Nq, shapes[order[k]].epb, shapes[order[k]].lay));
     }
     const int64_t ntiles = a.first_tile[nblocks];
     if (ntiles > kMaxTiles)

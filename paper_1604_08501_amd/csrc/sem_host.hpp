@@ -35,9 +35,16 @@ struct DefaultTile {
 };
 DefaultTile default_tile(sem_dtype dt, int nq);
 
-// Built-in batch shape of order nq in a launch of nt threads (the shape a
-// plan takes without autotuning); false if none fits.
-bool batch_default_shape(sem_dtype dt, int nt, int nq, int* epb, int* lay);
+// The blocks of a batch, as far as their tile shapes depend on them.
+struct BatchOrder {
+    int nq;
+    int64_t elements;
+};
+// Built-in batch shapes (those a plan takes without autotuning; rk: fused
+// Runge-Kutta stages) of every block, and the launch's workgroup size; 0 if
+// some order has none.
+int batch_default_shapes(sem_dtype dt, bool rk, const BatchOrder* orders, int n,
+                         DefaultTile* shapes);
 
 sem_status check_dtype(sem_dtype dt);
 sem_status check_order(int32_t Ne, int32_t Nq);

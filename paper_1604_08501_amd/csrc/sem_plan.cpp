@@ -428,47 +428,97 @@ sem_status autotune(PlanCore& p, bool use_cache, hipStream_t s)
     return SEM_OK;
 }
 
-// The built-in shape of one order in a launch of nt threads: the
-// single-order default tile, else the historical small shape with all fluxes
-// resident, else the same count aliased.  False if none fits.
-bool default_shape(sem_dtype dt, int nt, int nq, bool rk, int* epb, int* lay)
+// A built-in shape of one order in a launch of nt threads: the single-order
+// default tile, else the historical small shape with all fluxes resident, else
+// the same count aliased; of the shapes a fused stage can run (at most one node
+// per lane with all fluxes resident, two aliased) or of all.  False if none
+// fits.
+bool default_shape(sem_dtype dt, int nt, int nq, bool fused_only, int* epb, int* lay)
 {
     const DefaultTile dft = default_tile(dt, nq);
-    if (variant_ok(dt, nt, nq, dft.epb, dft.lay, rk)) {
+    if (variant_ok(dt, nt, nq, dft.epb, dft.lay, fused_only)) {
         *epb = dft.epb;
         *lay = dft.lay;
         return true;
     }
     *epb = default_epb(nq);
     for (int l : {(int)semk::FULL, (int)semk::ALIAS})
-        if (variant_ok(dt, nt, nq, *epb, l, rk)) {
+        if (variant_ok(dt, nt, nq, *epb, l, fused_only)) {
             *lay = l;
             return true;
         }
     return false;
 }
 
-// Built-in batch shapes (no autotuning): the smallest workgroup size among
-// 256, 512 and 1024 for which every order has a built-in shape.
-sem_status default_shapes(PlanCore& p)
+// Shapes of every order (epb and lay per entry) at the smallest workgroup size
+// that has them all; 0 if none has.
+int pick_shapes(sem_dtype dt, bool rk, bool dense, const BatchOrder* orders, int n,
+                DefaultTile* shapes)
 {
     for (int nt : semh::kBatchThreads) {
         bool all = true;
-        for (OrderChoice& o : p.orders)
-            all = all && default_shape(p.dtype, nt, o.nq, p.rk, &o.epb, &o.lay);
-        if (all) {
-            p.nt = nt;
-            return SEM_OK;
+        for (int i = 0; i < n && all; ++i) {
+            DefaultTile& t = shapes[i];
+            all = default_shape(dt, nt, orders[i].nq, !dense, &t.epb, &t.lay);
+            // FP64 at Nq = 4 keeps eight elements per tile: the static call's
+            // table is documented by them
+            if (!rk && !dense && dt == SEM_F64 && orders[i].nq == 4 && t.epb < 8)
+                all = false;
         }
+        if (all)
+            return nt;
     }
-    return fail(SEM_ERR_UNSUPPORTED, "no default batch shape covers every order of the plan");
+    return 0;
+}
+
+// Tiles of the blocks fit the static call's table.
+bool fits_static(const BatchOrder* orders, int n, const DefaultTile* shapes)
+{
+    int64_t tiles = 0;
+    for (int i = 0; i < n; ++i)
+        tiles += (orders[i].elements + shapes[i].epb - 1) / shapes[i].epb;
+    return tiles <= SEM_STATIC_MAX_TILES;
+}
+
+sem_status default_shapes(PlanCore& p)
+{
+    std::vector<BatchOrder> orders;   // per block: tiles do not span blocks
+    for (const sem_block& b : p.blocks)
+        orders.push_back({b.Nq, b.Ne});
+    std::vector<DefaultTile> shapes(orders.size());
+    p.nt = batch_default_shapes(p.dtype, p.rk, orders.data(), (int)orders.size(), shapes.data());
+    if (!p.nt)
+        return fail(SEM_ERR_UNSUPPORTED, "no default batch shape covers every order of the plan");
+    for (OrderChoice& o : p.orders)
+        for (size_t i = 0; i < orders.size(); ++i)
+            if (orders[i].nq == o.nq) {
+                o.epb = shapes[i].epb;
+                o.lay = shapes[i].lay;
+            }
+    return SEM_OK;
 }
 
 }  // namespace
 
-bool semapi::batch_default_shape(sem_dtype dt, int nt, int nq, int* epb, int* lay)
+// Built-in shapes are those a fused stage can run, whose small LDS and one or
+// two nodes per lane suit a plain launch too: they measured as fast as the
+// autotuned ones or up to 6% faster.  Shapes of up to four nodes per lane with
+// all fluxes resident put every tile of the launch under their LDS: 8 million
+// nodes in orders Nq = 4, 6, 8, 10 took 209 us in FP32 (now 136) and 465 in
+// FP64 (253), 2 to 5 236 (126) and 288 (286), 5, 7, 9 196 (151) and 602 (285).
+// They hold more elements per tile at Nq = 2, 3 and 5, though, so they stay
+// where only they fit the static call's tile table (a plan then takes them too,
+// for the same bits).
+int semapi::batch_default_shapes(sem_dtype dt, bool rk, const BatchOrder* orders, int n,
+                                 DefaultTile* shapes)
 {
-    return default_shape(dt, nt, nq, false, epb, lay);
+    const int nt = pick_shapes(dt, rk, false, orders, n, shapes);
+    if (rk || (nt && fits_static(orders, n, shapes)))
+        return nt;
+    const int dense = pick_shapes(dt, rk, true, orders, n, shapes);
+    if (!nt || (dense && fits_static(orders, n, shapes)))
+        return dense;
+    return pick_shapes(dt, rk, false, orders, n, shapes);
 }
 
 namespace {

@@ -7,6 +7,7 @@ import os
 import re
 
 import pytest
+import torch
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "sem.h")
@@ -452,3 +453,21 @@ def test_rhs_validation(L, sv):
     assert rhs(out=3 * B + 8) == sv.SEM_ERR_INVALID_ARG          # overlaps q
     assert rhs(out=5 * B + 16) == sv.SEM_ERR_INVALID_ARG         # overlaps the neighbour table
     assert b"overlaps nbr" in L.sem_last_error()
+
+
+@pytest.mark.parametrize("dtype,Nq,epb", [(0, 2, 64), (0, 3, 8), (0, 4, 8), (0, 5, 2), (0, 6, 1),
+                                          (1, 2, 128), (1, 3, 16), (1, 4, 2), (1, 5, 2), (1, 7, 1)])
+def test_batch_rhs_static_keeps_its_element_limit(L, sv, dtype, Nq, epb):
+    """The static table takes 32768 tiles of `epb` elements of one order; one
+    element more is rejected on the host.  (Fewer tiles pass this check: what
+    follows it needs a device.)"""
+    ph = sv.sem_phys(1e5, 1.4, 287.0, 9.81)
+    b = 1 << 44
+    for ne, rejected in ((32768 * epb, False), (32768 * epb + 1, True)):
+        block = (sv.sem_block * 1)(sv.sem_block(Nq, ne, b, b + (1 << 40), b + (2 << 40), None, None,
+                                                b + (3 << 40)))
+        if rejected:
+            assert L.sem_batch_rhs_static(block, 1, dtype, ctypes.byref(ph), None) == -1
+            assert b"static tile table" in L.sem_last_error()
+        elif not torch.cuda.is_available():
+            assert L.sem_batch_rhs_static(block, 1, dtype, ctypes.byref(ph), None) == -3
