@@ -258,6 +258,29 @@ template <int NQ>
 struct Shape {
     static constexpr int NQ2 = NQ * NQ;
     static constexpr int M = NQ * NQ * NQ;
+    // Which per-node accesses stream.  A field of an element is a run of M
+    // values; where that is not whole 128-byte lines, the line at its end also
+    // holds the start of the next run, which other lanes or another wave read,
+    // and a streamed line is often gone by then.  The shorter the run, the
+    // larger the shared part: reading through the cache takes 0.64 of the time
+    // at 32 bytes (FP32, Nq = 2), 0.82 at 108, 0.92 at 216 and 500 bytes, 0.97
+    // at 1372 (FP32, Nq = 7; 0.87 on the 5003-element call) and 0.99 at 1000
+    // (FP64, Nq = 5), but 1.03 at 1728 and 8000 bytes (FP64, Nq = 6 and 10).
+    // Stores, and the loads of an rhs that is accumulated into, gain only in
+    // runs shorter than a line (0.90 at 32 bytes, 0.96 at 108; 1.02 at 216, 1.16
+    // at 1000; an accumulating load 1.03 at 864 and 1372).  v + s keeps its
+    // metric terms streaming at every order: the cache there holds the state
+    // for the neighbours (1.09 at 500 bytes otherwise).
+    template <typename T>
+    static constexpr bool stream_loads()
+    {
+        return (M * sizeof(T)) % 128 == 0 || M * sizeof(T) >= 1500;
+    }
+    template <typename T>
+    static constexpr bool stream_stores()
+    {
+        return M * sizeof(T) >= 128;
+    }
     // D is staged in front of the flux area; pad it to 16 bytes
     template <typename T>
     static constexpr int d_slots()
@@ -381,36 +404,35 @@ struct RkNode<T, true> {
 
 // Epilogue for one node: rhs = -(1/J) acc + source (+ rhs when ACC), or the
 // fused Runge-Kutta stage out = a x + b (q + dt v) when RK (five fields).
+// STREAM: whether the accesses stream.
 template <typename T, int M, int NF, bool ACC, bool RK, bool STREAM = true>
 __device__ __forceinline__ void store_node(const BlockPtrs<T>& B, const RkStage& rk, int64_t e,
                                            int m, const T (&acc)[NF], T jinv, T src,
                                            const RkNode<T, RK>& rn)
 {
     static_assert(!RK || NF == 5, "the fused Runge-Kutta stage is for the five-field state");
+    auto ld = [](const T* p) { return STREAM ? ld_stream(p) : *p; };
     T* __restrict__ re = B.rhs + e * (NF * M) + m;
     T x[RK ? 5 : 1];
     if constexpr (RK) {
         const T* xe = B.rk_x + e * (5 * M) + m;
 #pragma unroll
         for (int b = 0; b < 5; ++b)
-            x[b] = rk.a != 0.0 ? ld_stream(xe + b * M) : (T)0;
+            x[b] = rk.a != 0.0 ? ld(xe + b * M) : (T)0;
     }
 #pragma unroll
     for (int b = 0; b < NF; ++b) {
         T v = -jinv * acc[b];
         if (b == 3)
             v += src;
-        if constexpr (RK) {
-            st_stream(re + b * M, (T)rk.a * x[b] + (T)rk.b * (rn.q[b] + (T)rk.dt * v));
-        } else if constexpr (STREAM) {
-            if constexpr (ACC)
-                v += ld_stream(re + b * M);
+        if constexpr (RK)
+            v = (T)rk.a * x[b] + (T)rk.b * (rn.q[b] + (T)rk.dt * v);
+        else if constexpr (ACC)
+            v += ld(re + b * M);
+        if constexpr (STREAM)
             st_stream(re + b * M, v);
-        } else {
-            if constexpr (ACC)
-                v += re[b * M];
+        else
             re[b * M] = v;
-        }
     }
 }
 
@@ -847,7 +869,8 @@ __device__ __forceinline__ void volume_tile_full(const BlockPtrs<T>& B, int64_t 
         const int es = t / M;
         const int m = t - es * M;
         NodeState<T, NF> st;
-        load_node<T, M, NF, DIRS, GEOE>(B, ph, e0 + es, m, st);
+        load_node<T, M, NF, DIRS, GEOE, Shape<NQ>::template stream_loads<T>()>(B, ph, e0 + es, m,
+                                                                              st);
         rn.load(B, rk, e0 + es, m, M, st);
         T* __restrict__ F = sF + es * (VPN * M) + m;
         if constexpr (RREG) {
@@ -879,7 +902,8 @@ __device__ __forceinline__ void volume_tile_full(const BlockPtrs<T>& B, int64_t 
             if ((LD >> d) & 1)
                 contract_dir<T, NQ, M, NF, UNR>(sD, Fe + dir_slot<LD>(d) * (NF * M), d, i, j, k,
                                                 acc);
-        store_node<T, M, NF, ACC, RK>(B, rk, e0 + es, m, acc, jinv, src, rn);
+        store_node<T, M, NF, ACC, RK, Shape<NQ>::template stream_stores<T>()>(B, rk, e0 + es, m, acc,
+                                                                              jinv, src, rn);
     };
 
     if constexpr (NPT == 1) {
@@ -965,7 +989,8 @@ __device__ __forceinline__ void volume_tile_alias(const BlockPtrs<T>& B, int64_t
             acc[p][b] = (T)0;
         if (live[p]) {
             const int es = t / M;
-            load_node<T, M, NF, DIRS, GEOE, true, true, SURF>(B, ph, e0 + es, t - es * M, st[p]);
+            load_node<T, M, NF, DIRS, GEOE, SURF || Shape<NQ>::template stream_loads<T>(), true,
+                      SURF>(B, ph, e0 + es, t - es * M, st[p]);
             rn[p].load(B, rk, e0 + es, t - es * M, M, st[p]);
         }
     }
@@ -1030,8 +1055,8 @@ __device__ __forceinline__ void volume_tile_alias(const BlockPtrs<T>& B, int64_t
                 gather_face_terms<T, NQ>(m % NQ, (m / NQ) % NQ, m / NQ2,
                                          sv.sFace + es * (kFaceVals * 6 * NQ2), sv.lift, acc[p]);
             }
-            store_node<T, M, NF, ACC, RK>(B, rk, e0 + es, t - es * M, acc[p], st[p].jinv,
-                                          st[p].src, rn[p]);
+            store_node<T, M, NF, ACC, RK, Shape<NQ>::template stream_stores<T>()>(
+                B, rk, e0 + es, t - es * M, acc[p], st[p].jinv, st[p].src, rn[p]);
         }
 }
 
@@ -1440,6 +1465,7 @@ __device__ __forceinline__ void adjoint_tile(const AdjPtrs<T>& B, int64_t e0, in
     T* __restrict__ sD = smem;
     T* __restrict__ sW = smem + Shape<NQ>::template d_slots<T>();
     const int tid = threadIdx.x;
+    auto ld = [](const T* p) { return Shape<NQ>::template stream_loads<T>() ? ld_stream(p) : *p; };
 
     for (int x = tid; x < NQ2; x += NT)
         sD[x] = B.D[x];
@@ -1458,16 +1484,16 @@ __device__ __forceinline__ void adjoint_tile(const AdjPtrs<T>& B, int64_t e0, in
             T lb[5];
 #pragma unroll
             for (int b = 0; b < 5; ++b)
-                lb[b] = ld_stream(le + b * M);
-            const T jinv = ld_stream(ge + 9 * M);
-            const T rho = ld_stream(qe);
-            nd[p].U1 = ld_stream(qe + M);
-            nd[p].U2 = ld_stream(qe + 2 * M);
-            nd[p].U3 = ld_stream(qe + 3 * M);
-            nd[p].Th = ld_stream(qe + 4 * M);
+                lb[b] = ld(le + b * M);
+            const T jinv = ld(ge + 9 * M);
+            const T rho = ld(qe);
+            nd[p].U1 = ld(qe + M);
+            nd[p].U2 = ld(qe + 2 * M);
+            nd[p].U3 = ld(qe + 3 * M);
+            nd[p].Th = ld(qe + 4 * M);
 #pragma unroll
             for (int s = 0; s < 9; ++s)
-                nd[p].g[s] = ld_stream(ge + s * M);
+                nd[p].g[s] = ld(ge + s * M);
             T* W = sW + es * (5 * M) + m;
 #pragma unroll
             for (int b = 0; b < 5; ++b)
@@ -1546,9 +1572,15 @@ __device__ __forceinline__ void adjoint_tile(const AdjPtrs<T>& B, int64_t e0, in
 #pragma unroll
             for (int b = 0; b < 5; ++b) {
                 T v = out[b];
-                if constexpr (ACC)
-                    v += ld_stream(me + b * M);
-                st_stream(me + b * M, v);
+                if constexpr (Shape<NQ>::template stream_stores<T>()) {
+                    if constexpr (ACC)
+                        v += ld_stream(me + b * M);
+                    st_stream(me + b * M, v);
+                } else {
+                    if constexpr (ACC)
+                        v += me[b * M];
+                    me[b * M] = v;
+                }
             }
         }
     }
