@@ -442,7 +442,7 @@ __device__ __forceinline__ void store_node(const BlockPtrs<T>& B, const RkStage&
 template <typename T, int NF>
 struct NodeState {
     T rho, U1, U2, U3, Th, rinv, pp, jinv, src;
-    T pfull;   // full pressure (FULLP loads only)
+    T pfull;   // full pressure (v + s tiles only)
     T g[9];
     T Q[NF > 5 ? NF - 5 : 1];
 };
@@ -452,11 +452,8 @@ struct NodeState {
 // reads through the cache (for tiles whose consecutive accesses share cache
 // lines).  SRC = false leaves the gravity source out (src = 0, rho_ref not
 // read), for a pass that adds one direction's term to a finished rhs.
-// FULLP = true also keeps the full pressure (for the surface term) and reads
-// the state and Theta_ref through the cache: the face neighbours of the
-// element read its face values again.
 template <typename T, int M, int NF, int DIRS, bool GEOE = false, bool STREAM = true,
-          bool SRC = true, bool FULLP = false>
+          bool SRC = true>
 __device__ __forceinline__ void load_node(const BlockPtrs<T>& B, const Phys& ph, int64_t e, int m,
                                           NodeState<T, NF>& st)
 {
@@ -466,17 +463,16 @@ __device__ __forceinline__ void load_node(const BlockPtrs<T>& B, const Phys& ph,
     // per-element metric records are shared by every node of the element and
     // stay cached; everything else streams
     auto ld = [](const auto* p) { return STREAM ? ld_stream(p) : *p; };
-    auto ldq = [](const auto* p) { return (STREAM && !FULLP) ? ld_stream(p) : *p; };
     auto geo_at = [&](int s) { return GEOE ? ge[s * GS] : ld(ge + s * GS); };
-    const T rho = ldq(qe);
+    const T rho = ld(qe);
     st.rho = rho;
-    st.U1 = ldq(qe + M);
-    st.U2 = ldq(qe + 2 * M);
-    st.U3 = ldq(qe + 3 * M);
-    st.Th = ldq(qe + 4 * M);
+    st.U1 = ld(qe + M);
+    st.U2 = ld(qe + 2 * M);
+    st.U3 = ld(qe + 3 * M);
+    st.Th = ld(qe + 4 * M);
 #pragma unroll
     for (int b = 5; b < NF; ++b)
-        st.Q[b - 5] = ldq(qe + b * M);
+        st.Q[b - 5] = ld(qe + b * M);
 #pragma unroll
     for (int s = 0; s < 9; ++s)
         st.g[s] = ((DIRS >> (s / 3)) & 1) ? geo_at(s) : (T)0;
@@ -487,13 +483,10 @@ __device__ __forceinline__ void load_node(const BlockPtrs<T>& B, const Phys& ph,
     if (has_ref) {
         if constexpr (SRC)
             rr = ld(B.rho_ref + e * M + m);
-        thr = ldq(B.theta_ref + e * M + m);
+        thr = ld(B.theta_ref + e * M + m);
     }
     st.src = SRC ? -(T)ph.grav * (rho - rr) : (T)0;
-    if constexpr (FULLP)
-        Pressure<T>::eval_full(st.Th, has_ref, thr, ph, st.pp, st.pfull);
-    else
-        st.pp = Pressure<T>::eval(st.Th, has_ref, thr, ph);
+    st.pp = Pressure<T>::eval(st.Th, has_ref, thr, ph);
     st.rinv = recip(rho);
 }
 
@@ -639,21 +632,6 @@ __device__ __forceinline__ int64_t xcd_contiguous_block(int64_t b, int64_t G)
     return (b % kXcds) * per + b / kXcds;
 }
 
-// Values staged per neighbour face node: the state (5), the flux pressure
-// and the sound speed sqrt(gamma p / rho) of the full pressure.
-constexpr int kFaceVals = 7;
-
-// Values staged per own face node by its owner: the state (5), the flux
-// pressure, the sound speed, the outward normal times its area factor (3)
-// and 1/rho.
-constexpr int kOwnVals = 11;
-
-template <int NQ>
-constexpr int face_lds_values_per_element()
-{
-    return 6 * (kFaceVals + kOwnVals) * NQ * NQ;
-}
-
 // Node of face (d, side) with tangential indices (a2, b2).
 template <int NQ>
 __device__ __forceinline__ int face_node(int d, int side, int a2, int b2)
@@ -664,140 +642,34 @@ __device__ __forceinline__ int face_node(int d, int side, int a2, int b2)
     return (side ? NQ - 1 : 0) * sd + a2 * sa + b2 * sb;
 }
 
-// The tile's neighbour face values into LDS, sF[es][f][v][a2 + NQ b2]: for
-// face f of tile element es, the state of the element across f at its node
-// facing ours, its flux pressure and its sound speed.  Faces whose neighbour
-// index lies outside [0, Ne) are boundary faces: nothing is read.
-template <typename T, int NQ, int EPB, int NT>
-__device__ __forceinline__ void stage_neighbour_faces(const BlockPtrs<T>& B,
-                                                      const int32_t* __restrict__ nbr,
-                                                      const Phys& ph, int64_t e0, int ne,
-                                                      T* __restrict__ sFace)
+// F* - Fn(q-) of the five fields at a face node: the states, flux pressures,
+// sound speeds and reciprocal densities of both sides (m: this element's, p:
+// the neighbour's) and the outward normal n times its area factor.
+template <typename T>
+__device__ __forceinline__ void face_flux(const T (&qm)[5], const T (&qp)[5], T pm, T pp, T cm,
+                                          T cp, T rinv_m, T rinv_p, const T (&n)[3], T (&out)[5])
 {
-    constexpr int NQ2 = NQ * NQ;
-    constexpr int M = NQ2 * NQ;
-    constexpr int PER = 6 * NQ2;
-    const bool has_ref = B.theta_ref != nullptr;
-    const T gam = (T)ph.gamma;
-#pragma unroll 1
-    for (int x = threadIdx.x; x < EPB * PER; x += NT) {
-        const int es = x / PER;
-        const int r = x - es * PER;
-        const int f = r / NQ2;
-        const int a = r - f * NQ2;
-        if (es >= ne)
-            continue;
-        const int64_t en = nbr[(e0 + es) * 6 + f];
-        if (en < 0 || en >= B.Ne)
-            continue;
-        const int d = f >> 1, side = f & 1;
-        const int mp = face_node<NQ>(d, 1 - side, a % NQ, a / NQ);
-        const T* __restrict__ qn = B.q + en * (5 * M) + mp;
-        T v[kFaceVals];
+    const T nn = root(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
+    const T NUm = n[0] * qm[1] + n[1] * qm[2] + n[2] * qm[3];
+    const T NUp = n[0] * qp[1] + n[1] * qp[2] + n[2] * qp[3];
+    const T vm = NUm * rinv_m, vp = NUp * rinv_p;   // N . u on each side
+    const T inn = recip(nn);
+    const T lam_m = fabs(vm) * inn + cm;
+    const T lam_p = fabs(vp) * inn + cp;
+    const T diss = (T)0.5 * (lam_m > lam_p ? lam_m : lam_p) * nn;
+    const T dp = pp - pm;
+    const T dF[5] = {NUp - NUm, qp[1] * vp - qm[1] * vm + n[0] * dp,
+                     qp[2] * vp - qm[2] * vm + n[1] * dp, qp[3] * vp - qm[3] * vm + n[2] * dp,
+                     qp[4] * vp - qm[4] * vm};
 #pragma unroll
-        for (int b = 0; b < 5; ++b)
-            v[b] = qn[b * M];
-        const double thr = has_ref ? B.theta_ref[en * M + mp] : 0.0;
-        T pfull;
-        Pressure<T>::eval_full(v[4], has_ref, thr, ph, v[5], pfull);
-        v[6] = root(gam * pfull / v[0]);
-        T* __restrict__ o = sFace + es * (kFaceVals * PER) + f * (kFaceVals * NQ2) + a;
-#pragma unroll
-        for (int b = 0; b < kFaceVals; ++b)
-            o[b * NQ2] = v[b];
-    }
-}
-
-// The owner of a boundary node stages, for each face of the element the node
-// lies on, the node's state, flux pressure, sound speed, outward normal N
-// (sigma (g_0d, g_1d, g_2d) at the node) and 1/rho in sOwn[f][v][a].
-template <typename T, int NQ>
-__device__ __forceinline__ void stage_own_faces(const NodeState<T, 5>& st, int i, int j, int k,
-                                                T gam, T* __restrict__ sOwn)
-{
-    constexpr int NQ2 = NQ * NQ;
-    constexpr int N = NQ - 1;
-    const int ijk[3] = {i, j, k};
-    if (!(i == 0 || i == N || j == 0 || j == N || k == 0 || k == N))
-        return;
-    const T c = root(gam * st.pfull * st.rinv);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const int id = ijk[d];
-        if (id != 0 && id != N)
-            continue;
-        const int side = id == N ? 1 : 0;
-        const int a = d == 0 ? j + NQ * k : (d == 1 ? i + NQ * k : i + NQ * j);
-        const T sg = side ? (T)1 : (T)-1;
-        const T v[kOwnVals] = {st.rho, st.U1, st.U2, st.U3, st.Th, st.pp, c,
-                               sg * st.g[3 * d], sg * st.g[3 * d + 1], sg * st.g[3 * d + 2],
-                               st.rinv};
-        T* __restrict__ o = sOwn + (2 * d + side) * (kOwnVals * NQ2) + a;
-#pragma unroll
-        for (int b = 0; b < kOwnVals; ++b)
-            o[b * NQ2] = v[b];
-    }
-}
-
-// One thread per face node of the tile: F* - Fn(q-) of the five fields from
-// the staged own and neighbour values, written over the neighbour's state in
-// sFace (zero for a boundary face).
-template <typename T, int NQ, int EPB, int NT>
-__device__ __forceinline__ void face_fluxes(const int32_t* __restrict__ nbr, int64_t Ne, int64_t e0,
-                                            int ne, T* __restrict__ sFace,
-                                            const T* __restrict__ sOwn)
-{
-    constexpr int NQ2 = NQ * NQ;
-    constexpr int PER = 6 * NQ2;
-#pragma unroll 1
-    for (int x = threadIdx.x; x < EPB * PER; x += NT) {
-        const int es = x / PER;
-        const int r = x - es * PER;
-        const int f = r / NQ2;
-        const int a = r - f * NQ2;
-        if (es >= ne)
-            continue;
-        T* __restrict__ v = sFace + es * (kFaceVals * PER) + f * (kFaceVals * NQ2) + a;
-        const int64_t en = nbr[(e0 + es) * 6 + f];
-        if (en < 0 || en >= Ne) {
-#pragma unroll
-            for (int b = 0; b < 5; ++b)
-                v[b * NQ2] = (T)0;   // boundary face: exterior state = interior state
-            continue;
-        }
-        const T* __restrict__ o = sOwn + es * (kOwnVals * PER) + f * (kOwnVals * NQ2) + a;
-        T qm[5], qp[5];
-#pragma unroll
-        for (int b = 0; b < 5; ++b) {
-            qm[b] = o[b * NQ2];
-            qp[b] = v[b * NQ2];
-        }
-        const T pm = o[5 * NQ2], cm = o[6 * NQ2];
-        const T n0 = o[7 * NQ2], n1 = o[8 * NQ2], n2 = o[9 * NQ2], rinv_m = o[10 * NQ2];
-        const T pp = v[5 * NQ2], cp = v[6 * NQ2];
-        const T nn = root(n0 * n0 + n1 * n1 + n2 * n2);
-        const T rinv_p = recip(qp[0]);
-        const T NUm = n0 * qm[1] + n1 * qm[2] + n2 * qm[3];
-        const T NUp = n0 * qp[1] + n1 * qp[2] + n2 * qp[3];
-        const T vm = NUm * rinv_m, vp = NUp * rinv_p;   // N . u on each side
-        const T inn = recip(nn);
-        const T lam_m = fabs(vm) * inn + cm;
-        const T lam_p = fabs(vp) * inn + cp;
-        const T diss = (T)0.5 * (lam_m > lam_p ? lam_m : lam_p) * nn;
-        const T dp = pp - pm;
-        const T dF[5] = {NUp - NUm, qp[1] * vp - qm[1] * vm + n0 * dp,
-                         qp[2] * vp - qm[2] * vm + n1 * dp, qp[3] * vp - qm[3] * vm + n2 * dp,
-                         qp[4] * vp - qm[4] * vm};
-#pragma unroll
-        for (int b = 0; b < 5; ++b)
-            v[b * NQ2] = (T)0.5 * dF[b] - diss * (qp[b] - qm[b]);
-    }
+    for (int b = 0; b < 5; ++b)
+        out[b] = (T)0.5 * dF[b] - diss * (qp[b] - qm[b]);
 }
 
 // acc[b] += (1/w_N) sum over the node's faces of (F* - Fn(q-))_b, so that the
 // epilogue's -(1/J) acc + source is v + s; faces visited r, s, t in order.
 // sFe: the element's face results, VALS values per face node slot.
-template <typename T, int NQ, int VALS = kFaceVals>
+template <typename T, int NQ, int VALS>
 __device__ __forceinline__ void gather_face_terms(int i, int j, int k,
                                                   const T* __restrict__ sFe, T lift, T (&acc)[5])
 {
@@ -823,16 +695,6 @@ __device__ __forceinline__ void gather_face_terms(int i, int j, int k,
     for (int b = 0; b < 5; ++b)
         acc[b] += lift * sacc[b];
 }
-
-// Inputs of the fused surface term: the neighbour table, 1/w_N, and the
-// LDS of the staged neighbour faces.
-template <typename T>
-struct SurfIn {
-    const int32_t* nbr;
-    T lift;
-    T* sFace;   // [EPB][6][kFaceVals][Nq^2]: neighbour values, then F* - Fn(q-)
-    T* sOwn;    // [EPB][6][kOwnVals][Nq^2]: the element's own face values
-};
 
 // ---------------------------------------------------------------------------
 // Forward tile: EPB elements starting at e0, of which the first ne exist.
@@ -947,18 +809,12 @@ __device__ __forceinline__ void volume_tile_full(const BlockPtrs<T>& B, int64_t 
     }
 }
 
-// SURF: rhs = v + s, with the neighbour faces staged in sv.sFace during the
-// state loads and the face terms added in the epilogue (five fields, all
-// three directions).
 template <typename T, int NQ, int EPB, int NT, bool ACC, bool RK, int NF, int DIRS, bool GEOE,
-          int UNR = 2, bool SURF = false>
+          int UNR = 2>
 __device__ __forceinline__ void volume_tile_alias(const BlockPtrs<T>& B, int64_t e0, int ne,
                                                   const Phys& ph, const RkStage& rk,
-                                                  T* __restrict__ smem,
-                                                  const SurfIn<T>& sv = SurfIn<T>{})
+                                                  T* __restrict__ smem)
 {
-    static_assert(!SURF || (NF == 5 && DIRS == 7 && !GEOE), "the fused surface term is for the "
-                                                            "five-field r+s+t volume term");
     constexpr int NQ2 = Shape<NQ>::NQ2;
     constexpr int M = Shape<NQ>::M;
     constexpr int NODES = EPB * M;
@@ -989,22 +845,10 @@ __device__ __forceinline__ void volume_tile_alias(const BlockPtrs<T>& B, int64_t
             acc[p][b] = (T)0;
         if (live[p]) {
             const int es = t / M;
-            load_node<T, M, NF, DIRS, GEOE, SURF || Shape<NQ>::template stream_loads<T>(), true,
-                      SURF>(B, ph, e0 + es, t - es * M, st[p]);
+            load_node<T, M, NF, DIRS, GEOE, Shape<NQ>::template stream_loads<T>()>(
+                B, ph, e0 + es, t - es * M, st[p]);
             rn[p].load(B, rk, e0 + es, t - es * M, M, st[p]);
         }
-    }
-    if constexpr (SURF) {
-        stage_neighbour_faces<T, NQ, EPB, NT>(B, sv.nbr, ph, e0, ne, sv.sFace);
-#pragma unroll
-        for (int p = 0; p < NPT; ++p)
-            if (live[p]) {
-                const int t = tid + p * NT;
-                const int es = t / M;
-                const int m = t - es * M;
-                stage_own_faces<T, NQ>(st[p], m % NQ, (m / NQ) % NQ, m / NQ2, (T)ph.gamma,
-                                       sv.sOwn + es * (kOwnVals * 6 * NQ2));
-            }
     }
     if constexpr (RREG) {
 #pragma unroll
@@ -1040,21 +884,11 @@ __device__ __forceinline__ void volume_tile_alias(const BlockPtrs<T>& B, int64_t
                                                 m / NQ2, acc[p]);
             }
     }
-    if constexpr (SURF) {
-        // the staged faces were written before the first direction's barrier
-        face_fluxes<T, NQ, EPB, NT>(sv.nbr, B.Ne, e0, ne, sv.sFace, sv.sOwn);
-        __syncthreads();
-    }
 #pragma unroll
     for (int p = 0; p < NPT; ++p)
         if (live[p]) {
             const int t = tid + p * NT;
             const int es = t / M;
-            if constexpr (SURF) {
-                const int m = t - es * M;
-                gather_face_terms<T, NQ>(m % NQ, (m / NQ) % NQ, m / NQ2,
-                                         sv.sFace + es * (kFaceVals * 6 * NQ2), sv.lift, acc[p]);
-            }
             store_node<T, M, NF, ACC, RK, Shape<NQ>::template stream_stores<T>()>(
                 B, rk, e0 + es, t - es * M, acc[p], st[p].jinv, st[p].src, rn[p]);
         }

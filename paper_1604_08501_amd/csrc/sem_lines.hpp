@@ -6,67 +6,223 @@
 // values once, multiplies them by D on the matrix cores (D sits in a few
 // registers per lane) and writes the Nq results over them.  Per node and flux
 // that is one read and one write, whatever Nq, and D takes no LDS bandwidth.
-// On gfx950 an LDS read moves 256 bytes a cycle and a write 128, so a
-// transformed flux costs an LDS cycle count of about 12 per 64 nodes and
-// direction in FP64 against 20 and the reads of D (Nq = 8).
+// FP64 products run on the FP64 vector units' hardware, at their rate (64
+// TFLOP/s measured for the 4x4x4 shape), so they save LDS traffic and
+// instructions, not multiplications; FP32 ones run at twice the scalar rate.
 #pragma once
 #include "sem_device.hpp"
+#include "sem_pow.hpp"
 
 namespace semk {
 
-// LDS layout of one staged array (one field of one element) at Nq = 8 in
-// FP64: the word of node (i, j, k).  The low bits are permuted by an XOR of
-// index bits (pos is linear over bits), so that every access of a wave
-// touches each bank once: nodes in order, and 16 lines by 4 nodes along r, s
-// or t, reads in groups of 32 lanes (64 banks) and writes in groups of 16
-// (32 banks).  In node order the r lines' writes take eight times as long.
+typedef float float4_t __attribute__((ext_vector_type(4)));
+
+// LDS layout of one staged array (one field of one element): the word of
+// node (i, j, k), and the number of words.
+//   FP64, Nq = 8: the low bits are permuted by an XOR of index bits (pos is
+//   linear over bits), so that every access of a wave touches each bank once:
+//   nodes in order, and 16 lines by 4 nodes along r, s or t, reads in groups of
+//   32 lanes (64 banks) and writes in groups of 16 (32 banks).  In node order
+//   the r lines' writes take eight times as long.
+//   FP64, otherwise: node order.
+//   FP32: rows padded to an odd length, so that lanes on consecutive rows
+//   (the r lines) start in different banks.
+template <typename T, int NQ>
 struct LineLds {
-    static constexpr int WORDS = 512;
+    static constexpr bool XOR = sizeof(T) == 8 && NQ == 8;
+    static constexpr int P1 = sizeof(T) == 4 ? (NQ | 1) : NQ;
+    static constexpr int P2 = P1 * NQ;
+    static constexpr int WORDS = P2 * NQ;
     static __device__ __forceinline__ constexpr int pos(int i, int j, int k)
     {
-        return 64 * k + 8 * (j ^ (3 * (k & 1))) + (i ^ ((j >> 1) & 3) ^ (4 * (k & 1)));
+        if constexpr (XOR)
+            return 64 * k + 8 * (j ^ (3 * (k & 1))) + (i ^ ((j >> 1) & 3) ^ (4 * (k & 1)));
+        else
+            return i + P1 * j + P2 * k;
+    }
+    // word of position n of line (u, v) along direction d: r lines (j, k),
+    // s lines (i, k), t lines (i, j)
+    static __device__ __forceinline__ constexpr int line_pos(int d, int u, int v, int n)
+    {
+        return d == 0 ? pos(n, u, v) : (d == 1 ? pos(u, n, v) : pos(u, v, n));
     }
 };
 
-// Applies D along t to NARR consecutive staged arrays, in place; the caller's
-// wave takes the arrays first, first + STEP, ...
-// v_mfma_f64_4x4x4 multiplies four 4x4 blocks at once.  Lane l holds row l % 4,
-// column l / 16 of the left operand, and row l / 16 of column l % 16 (16 lines
-// side by side) of the right operand and of the result.
-template <int NARR, int STEP>
-__device__ __forceinline__ void transform_t_lines(const double* __restrict__ sD,
-                                                  double* __restrict__ sF, int first)
-{
-    constexpr int NG = 4;   // groups of 16 lines per array
-    const int l = threadIdx.x & 63;
-    const int c = l & 15, kk = l >> 4;
-    double a[2][2];
+// D in the operand layout of the matrix product, one copy per wave.
+template <typename T, int NQ>
+struct LineD;
+
+// FP64: v_mfma_f64_4x4x4 multiplies four 4x4 blocks at once.  Lane l holds
+// row l % 4, column l / 16 of the left operand (D, padded by zeros to whole
+// blocks), and row l / 16 of column l % 16 (16 lines side by side) of the
+// right operand and of the result.
+template <int NQ>
+struct LineD<double, NQ> {
+    static constexpr int KT = (NQ + 3) / 4;
+    static constexpr int PER = 16;   // lines at a time
+    double a[KT][KT];
+    __device__ __forceinline__ void load(const double* __restrict__ D)
+    {
+        const int l = threadIdx.x & 63;
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+        for (int rt = 0; rt < KT; ++rt)
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-            a[rt][kt] = sD[(4 * rt + (l & 3)) * 8 + 4 * kt + kk];
-    int off[NG];
-#pragma unroll
-    for (int g = 0; g < NG; ++g)
-        off[g] = LineLds::pos(c & 7, 2 * g + (c >> 3), kk);
-    constexpr int HALF = LineLds::pos(0, 0, 4);   // from node kk to node 4 + kk of a line
-#pragma unroll 1
-    for (int x = first; x < NARR; x += STEP) {
-        double* __restrict__ F = sF + x * LineLds::WORDS;
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            const double b0 = F[off[g]], b1 = F[off[g] ^ HALF];
-            double r[2];
-#pragma unroll
-            for (int rt = 0; rt < 2; ++rt) {
-                r[rt] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[rt][0], b0, 0.0, 0, 0, 0);
-                r[rt] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[rt][1], b1, r[rt], 0, 0, 0);
+            for (int kt = 0; kt < KT; ++kt) {
+                const int row = 4 * rt + (l & 3), col = 4 * kt + (l >> 4);
+                a[rt][kt] = row < NQ && col < NQ ? D[row * NQ + col] : 0.0;
             }
-            F[off[g]] = r[0];
-            F[off[g] ^ HALF] = r[1];
+    }
+    // D applied to this lane's line, whose node n is F[n * STEP], in place
+    template <int STEP>
+    __device__ __forceinline__ void apply(double* __restrict__ F, bool live) const
+    {
+        const int kk = (threadIdx.x & 63) >> 4;
+        double b[KT], r[KT];
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt)   // nodes past the line enter as zeros
+            b[kt] = 4 * kt + 3 < NQ || 4 * kt + kk < NQ ? F[(4 * kt + kk) * STEP] : 0.0;
+#pragma unroll
+        for (int rt = 0; rt < KT; ++rt) {
+            r[rt] = 0.0;
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt)
+                r[rt] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[rt][kt], b[kt], r[rt], 0, 0, 0);
+        }
+        if (live) {
+#pragma unroll
+            for (int rt = 0; rt < KT; ++rt)
+                if (4 * rt + 3 < NQ || 4 * rt + kk < NQ)
+                    F[(4 * rt + kk) * STEP] = r[rt];
         }
     }
+};
+
+// FP32, lines of up to nine nodes: v_mfma_f32_4x4x1 multiplies 16 blocks at
+// once: lane l holds row l % 4 of the left operand (a column of D), the value
+// of line l of the right one, and four consecutive outputs of line l.  Longer
+// lines: v_mfma_f32_16x16x4, operands as in FP64 with 16 rows, results in rows
+// 4 (l / 16) .. + 3 of line l % 16; D then takes a register per four columns
+// instead of one per column and four rows.
+template <int NQ>
+struct LineD<float, NQ> {
+    static constexpr bool WIDE = NQ > 9;
+    static constexpr int RT = (NQ + 3) / 4;
+    static constexpr int PER = WIDE ? 16 : 64;
+    float a[WIDE ? 1 : RT][WIDE ? RT : NQ];
+    __device__ __forceinline__ void load(const float* __restrict__ D)
+    {
+        const int l = threadIdx.x & 63;
+        if constexpr (WIDE) {
+#pragma unroll
+            for (int kt = 0; kt < RT; ++kt) {
+                const int row = l & 15, col = 4 * kt + (l >> 4);
+                a[0][kt] = row < NQ && col < NQ ? D[row * NQ + col] : 0.0f;
+            }
+        } else {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                const int row = 4 * rt + (l & 3);
+#pragma unroll
+                for (int n = 0; n < NQ; ++n)
+                    a[rt][n] = row < NQ ? D[row * NQ + n] : 0.0f;
+            }
+        }
+    }
+    template <int STEP>
+    __device__ __forceinline__ void apply(float* __restrict__ F, bool live) const
+    {
+        if constexpr (WIDE) {
+            const int kk = (threadIdx.x & 63) >> 4;
+            float b[RT];
+#pragma unroll
+            for (int kt = 0; kt < RT; ++kt)
+                b[kt] = 4 * kt + 3 < NQ || 4 * kt + kk < NQ ? F[(4 * kt + kk) * STEP] : 0.0f;
+            float4_t o = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int kt = 0; kt < RT; ++kt)
+                o = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0][kt], b[kt], o, 0, 0, 0);
+            if (live) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (4 * kk + v < NQ)
+                        F[(4 * kk + v) * STEP] = o[v];
+            }
+        } else {
+            float4_t o[RT];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+                o[rt] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            float b[NQ];
+#pragma unroll
+            for (int n = 0; n < NQ; ++n)
+                b[n] = F[n * STEP];
+#pragma unroll
+            for (int n = 0; n < NQ; ++n)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    o[rt] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[rt][n], b[n], o[rt], 0, 0, 0);
+            if (live) {
+#pragma unroll
+                for (int n = 0; n < NQ; ++n)
+                    F[n * STEP] = o[n / 4][n % 4];
+            }
+        }
+    }
+};
+
+// Applies D along direction DIR to NARR consecutive staged arrays, in place, a
+// group of lines at a time; the groups first, first + NW, ... are this wave's.
+// Lanes past the last line repeat it and write nothing.
+template <typename T, int NQ, int DIR, int NARR, int NW>
+__device__ __forceinline__ void transform_lines(const LineD<T, NQ>& A, T* __restrict__ sF,
+                                                int first)
+{
+    using L = LineLds<T, NQ>;
+    static_assert(!L::XOR, "additive layouts");
+    constexpr int NQ2 = NQ * NQ;
+    constexpr int PER = LineD<T, NQ>::PER;
+    constexpr int LINES = NARR * NQ2;
+#pragma unroll 2
+    for (int g = first; g < (LINES + PER - 1) / PER; g += NW) {
+        const int q = PER * g + ((int)threadIdx.x & (PER - 1));
+        const bool live = LINES % PER == 0 || q < LINES;
+        const int line = live ? q : LINES - 1;
+        const int a = line / NQ2, r = line - a * NQ2;
+        A.template apply<L::line_pos(DIR, 0, 0, 1)>(
+            sF + a * L::WORDS + L::line_pos(DIR, r % NQ, r / NQ, 0), live);
+    }
+}
+
+// Wave that starts the transform of the staged direction at slot s: the groups
+// follow one another over the waves, across the directions.
+template <typename T, int NQ, int NARR, int NW>
+__device__ __forceinline__ int first_group(int s)
+{
+    constexpr int PER = LineD<T, NQ>::PER;
+    const int w = (int)threadIdx.x >> 6;
+    const int at = (s * ((NARR * NQ * NQ + PER - 1) / PER)) % NW;
+    return w >= at ? w - at : w - at + NW;
+}
+
+// Physical constants and pressure of a tile: FP64 takes x^gamma from tables in
+// LDS.
+template <typename T>
+using LinePhys = std::conditional_t<sizeof(T) == 8, PowPhys, Phys>;
+
+template <typename T>
+constexpr int pow_table_values()
+{
+    return sizeof(T) == 8 ? kPowTableValues : 0;
+}
+
+template <typename T>
+__device__ __forceinline__ void line_pressure(T Th, bool has_ref, double thr, const LinePhys<T>& ph,
+                                              T& pflux, T& pfull)
+{
+    if constexpr (sizeof(T) == 8)
+        table_pressure(Th, has_ref, thr, ph, pflux, pfull);
+    else
+        Pressure<T>::eval_full(Th, has_ref, thr, ph, pflux, pfull);
 }
 
 }  // namespace semk

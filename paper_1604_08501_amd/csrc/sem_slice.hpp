@@ -36,7 +36,7 @@ __device__ __forceinline__ void contract_slice(const double* __restrict__ sD,
                                                const double (&f)[NF], int at, int k,
                                                double* __restrict__ sF, double (&acc)[NF])
 {
-    using L = LineLds;
+    using L = LineLds<double, 8>;
     const int l = threadIdx.x & 63;
     const int line = l & 7, h = (l >> 3) & 1, kk = l >> 4;
     const int row_in = DIR == 0 ? 4 * h + (l & 3) : 2 * (l & 3) + h;
@@ -75,6 +75,47 @@ __device__ __forceinline__ void contract_slice(const double* __restrict__ sD,
     }
 }
 
+// Applies D along t to NARR consecutive staged arrays, in place; the caller's
+// wave takes the arrays first, first + STEP, ...
+// v_mfma_f64_4x4x4 multiplies four 4x4 blocks at once.  Lane l holds row l % 4,
+// column l / 16 of the left operand, and row l / 16 of column l % 16 (16 lines
+// side by side) of the right operand and of the result.
+template <int NARR, int STEP>
+__device__ __forceinline__ void transform_t_lines(const double* __restrict__ sD,
+                                                  double* __restrict__ sF, int first)
+{
+    constexpr int NG = 4;   // groups of 16 lines per array
+    const int l = threadIdx.x & 63;
+    const int c = l & 15, kk = l >> 4;
+    double a[2][2];
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+            a[rt][kt] = sD[(4 * rt + (l & 3)) * 8 + 4 * kt + kk];
+    int off[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+        off[g] = LineLds<double, 8>::pos(c & 7, 2 * g + (c >> 3), kk);
+    constexpr int HALF = LineLds<double, 8>::pos(0, 0, 4);   // from node kk to node 4 + kk of a line
+#pragma unroll 1
+    for (int x = first; x < NARR; x += STEP) {
+        double* __restrict__ F = sF + x * LineLds<double, 8>::WORDS;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const double b0 = F[off[g]], b1 = F[off[g] ^ HALF];
+            double r[2];
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) {
+                r[rt] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[rt][0], b0, 0.0, 0, 0, 0);
+                r[rt] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[rt][1], b1, r[rt], 0, 0, 0);
+            }
+            F[off[g]] = r[0];
+            F[off[g] ^ HALF] = r[1];
+        }
+    }
+}
+
 // Own face values the v + s tile stages per face node: the state, the flux
 // pressure, the sound speed and the outward normal times its area factor.
 constexpr int kSliceOwnVals = 10;
@@ -82,7 +123,7 @@ constexpr int kSliceOwnVals = 10;
 template <int NF, bool SURF>
 constexpr int slice_lds_values()
 {
-    return NF * LineLds::WORDS + kPowTableValues + 64 + (SURF ? 6 * kSliceOwnVals * 64 : 0);
+    return NF * LineLds<double, 8>::WORDS + kPowTableValues + 64 + (SURF ? 6 * kSliceOwnVals * 64 : 0);
 }
 
 // Element e: the volume term of NF fields over DIRS, or v + s (SURF).
@@ -92,7 +133,7 @@ __device__ __forceinline__ void slice_tile(const BlockPtrs<double>& B, const int
                                            double* __restrict__ smem)
 {
     static_assert(!SURF || (NF == 5 && DIRS == 7 && !GEOE), "v + s is for the full volume term");
-    using L = LineLds;
+    using L = LineLds<double, 8>;
     constexpr int M = 512, N = 7;
     double* __restrict__ sF = smem;
     double* __restrict__ sTab = smem + NF * L::WORDS;
@@ -211,7 +252,7 @@ __device__ __forceinline__ void slice_tile(const BlockPtrs<double>& B, const int
                     for (int b = 0; b < 5; ++b)
                         qm[b] = o[b * 64];
                     const double pm = o[5 * 64], cm = o[6 * 64];
-                    const double n0 = o[7 * 64], n1 = o[8 * 64], n2 = o[9 * 64];
+                    const double n[3] = {o[7 * 64], o[8 * 64], o[9 * 64]};
                     // the node's sums wait in the slots just read, out of the
                     // registers (ten would spill to scratch memory, which ran
                     // 706 instead of 580 us)
@@ -219,30 +260,18 @@ __device__ __forceinline__ void slice_tile(const BlockPtrs<double>& B, const int
                     for (int b = 0; b < 5; ++b)
                         o[(5 + b) * 64] = acc[b];
                     asm volatile("" ::: "memory");
-                    const double nn = root(n0 * n0 + n1 * n1 + n2 * n2);
-                    const double NUm = n0 * qm[1] + n1 * qm[2] + n2 * qm[3];
-                    const double NUp = n0 * nq[1] + n1 * nq[2] + n2 * nq[3];
-                    // N . u on each side
-                    const double vm = NUm * recip(qm[0]), vp = NUp * recip(nq[0]);
-                    const double inn = recip(nn);
-                    const double lam_m = fabs(vm) * inn + cm;
-                    const double lam_p = fabs(vp) * inn + nc;
-                    const double diss = 0.5 * (lam_m > lam_p ? lam_m : lam_p) * nn;
-                    const double dp = np - pm;
-                    const double dF[5] = {NUp - NUm, nq[1] * vp - qm[1] * vm + n0 * dp,
-                                          nq[2] * vp - qm[2] * vm + n1 * dp,
-                                          nq[3] * vp - qm[3] * vm + n2 * dp,
-                                          nq[4] * vp - qm[4] * vm};
+                    double jump[5];
+                    face_flux(qm, nq, pm, np, cm, nc, recip(qm[0]), recip(nq[0]), n, jump);
 #pragma unroll
                     for (int b = 0; b < 5; ++b)
-                        o[b * 64] = 0.5 * dF[b] - diss * (nq[b] - qm[b]);
+                        o[b * 64] = jump[b];
                     asm volatile("" ::: "memory");
 #pragma unroll
                     for (int b = 0; b < 5; ++b)
                         acc[b] = o[(5 + b) * 64];
                 }
             }
-            // t lines: fields 0 and 3, 1 and 4 on the waves without a face, 2 on wave 0
+            // t lines on the waves without a face and, for the fifth field, wave 0
             if (w >= 6 || w == 0)
                 transform_t_lines<5, 3>(sD, sF, w >= 6 ? w - 6 : 2);
         } else {

@@ -353,3 +353,16 @@ def test_surface_and_rhs_deterministic(sv):
         c = host(sv.rhs(q, geo, D, nbr, rr, tr, ph))
         d = host(sv.rhs(q, geo, D, nbr, rr, tr, ph))
         assert np.array_equal(c, d)
+
+
+@pytest.mark.parametrize("Nq,fp32,ne", [(7, False, 768), (7, False, 769), (9, False, 768),
+                                        (9, False, 769), (10, False, 768), (10, False, 769),
+                                        (7, True, 2048), (7, True, 2049), (9, True, 2048),
+                                        (9, True, 2049), (10, True, 2048), (10, True, 2049)])
+def test_rhs_on_both_sides_of_the_lane_rule(sv, oracle_mod, Nq, fp32, ne):
+    """v + s takes one lane per node up to a number of elements and several
+    nodes per lane beyond it; a sub-mesh of that size has boundary faces.  The
+    forward gates."""
+    w = I.warped_workload(N=Nq - 1, n_side=13, n_elements=ne, k=320 + Nq)
+    e = err(host(run_rhs(sv, w, fp32=fp32)), oracle_vs(oracle_mod, w, fp32=fp32))
+    assert e.max() <= (2e-5 if fp32 else 1e-12), e
