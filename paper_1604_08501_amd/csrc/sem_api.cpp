@@ -256,8 +256,10 @@ extern "C" sem_status sem_volume_rhs_tiled(int32_t Ne, int32_t Nq, sem_dtype dty
     const DefaultTile dft = default_tile(dtype, Nq);
     int epb = tile && tile->elems_per_block > 0 ? tile->elems_per_block : 0;
     int lay = code == SEM_LAYOUT_DEFAULT ? -1 : internal_layout(code);
-    // no shape asked for: the slice tile where there is one
-    const bool slice = epb == 0 && lay < 0 && dtype == SEM_F64 && semh::use_slice<double>(Nq);
+    // no shape asked for: the order's own tile where there is one
+    const bool own = epb == 0 && lay < 0 &&
+                     (dtype == SEM_F64 ? semh::volume_own_tile<double>(Nq, Ne)
+                                       : semh::volume_own_tile<float>(Nq, Ne));
     if (epb == 0 && lay < 0) {
         epb = dft.epb;
         lay = dft.lay;
@@ -273,10 +275,12 @@ extern "C" sem_status sem_volume_rhs_tiled(int32_t Ne, int32_t Nq, sem_dtype dty
     const semk::Phys ph = to_phys(phys);
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t err;
-    if (slice)
-        err = semh::launch_volume_slice<double>(
-            5, 7, false, block_ptrs<double>(Ne, D, geo, q, rho_ref, theta_ref, rhs), ph, accumulate,
-            s);
+    if (own && dtype == SEM_F64)
+        err = semh::launch_volume_ext<double>(
+            Nq, 5, 7, block_ptrs<double>(Ne, D, geo, q, rho_ref, theta_ref, rhs), ph, accumulate, s);
+    else if (own)
+        err = semh::launch_volume_ext<float>(
+            Nq, 5, 7, block_ptrs<float>(Ne, D, geo, q, rho_ref, theta_ref, rhs), ph, accumulate, s);
     else if (dtype == SEM_F64)
         err = semh::launch_volume<double>(
             Nq, epb, lay, block_ptrs<double>(Ne, D, geo, q, rho_ref, theta_ref, rhs), ph, accumulate,

@@ -22,8 +22,6 @@ bool log_enabled();
 size_t elem_size(sem_dtype dt);
 semk::Phys to_phys(const sem_phys* p);
 
-constexpr int kMinNq = 2, kMaxNq = 10;
-
 // Historical small-order element counts (all fluxes resident).
 int default_epb(int nq);
 

@@ -23,6 +23,8 @@
     X(9, 1, 0) X(9, 1, 1)                                                      \
     X(10, 1, 0) X(10, 1, 1)
 
+constexpr int kMinNq = 2, kMaxNq = 10;   // orders of SEM_VARIANTS
+
 namespace semh {
 
 // A dispatch's work-item count (workgroups x lanes) is a 32-bit field of the
@@ -107,6 +109,102 @@ hipError_t launch_volume_slice(int nf, int dirs, bool per_element_geo,
 template <typename T>
 hipError_t launch_rhs_slice(const semk::BlockPtrs<T>& B, const int32_t* nbr, const semk::Phys& ph,
                             int accumulate, hipStream_t s);
+
+// Volume tiles on line transforms (sem_lines.hpp): elements of up to `nodes`
+// nodes together per workgroup (at least one element), up to `lanes` lanes,
+// all directions' fluxes staged at once or one direction's at a time.  Up to
+// `few` elements, and at any number where lanes = 0, the tile that contracts
+// node by node stays.
+struct LinePick {
+    int nodes, lanes;
+    bool all = false;
+    int few = 0;
+};
+
+// The faster of both tiles, and among the line tiles of 64-1024 lanes and
+// nodes, on 3.5 million nodes (per-element metric terms and five fields r+s+t
+// up to Nq = 10: 8 million), where it gained 3% or more.  The line tile wins
+// where the other one is held by its LDS reads or its few workgroups per CU:
+// orders that are no power of two, eight fields, metric terms that cost no
+// bandwidth.  us, node by node -> lines:
+//   per-element metric terms, FP64, Nq = 2, 4, 5, 6, 7, 9, 10, 12: 178 -> 166,
+//     157 -> 131, 182 -> 167, 187 -> 164, 219 -> 164, 224 -> 174, 209 -> 180,
+//     293 -> 232 (3: 174, lines 184)
+//   FP32, Nq = 3..9, 12: 98 -> 93, 74 -> 70, 91 -> 74, 101 -> 79, 110 -> 85,
+//     81 -> 72, 122 -> 90, 131 -> 96 (2: 92, lines 92; 10: 110, lines 104, but
+//     1000 elements 16.9, lines 19.7)
+//   five fields, r+s+t, FP64, Nq = 6, 7, 9, 12: 241 -> 230, 266 -> 245,
+//     279 -> 271, 183 -> 168; FP32, Nq = 6, 9, 12: 130 -> 121, 148 -> 130,
+//     79 -> 65
+//   five fields, r+s, FP64, Nq = 10: 132 -> 110; FP32, Nq = 6: 52.6 -> 51.0
+//   eight fields, r+s+t, FP64, Nq = 3, 5, 6, 7, 10, 12: 176 -> 159, 175 -> 159,
+//     172 -> 157, 262 -> 174, 215 -> 183, 277 -> 237; FP32, Nq = 5, 6, 7, 9, 12:
+//     87 -> 82, 85 -> 77, 95 -> 89, 98.9 -> 95.8, 103 -> 98
+//   eight fields, r+s, FP64, Nq = 3, 5, 10: 160 -> 149, 158 -> 145, 162 -> 154;
+//     FP32, Nq = 5, 6, 9: 81 -> 77, 75 -> 70, 85 -> 82
+// Few elements, of which a CU holds two or three: a tile of several nodes per
+// lane takes longer for one of them than the other tile (FP64, metric terms
+// per element: 512 elements of Nq = 9 15.3 us against 13.3, 256 of Nq = 12 17.8
+// against 16.8; five fields, r+s, 256 of Nq = 10 13.3 against 11.3; r+s+t, 1024
+// of Nq = 7 16.7 against 16.2).
+template <typename T>
+constexpr LinePick line_pick(int nq, int nf, int dirs, bool per_element_geo)
+{
+    constexpr LinePick none{0, 0};
+    constexpr bool f64 = sizeof(T) == 8;
+    if (nq > 12)
+        return none;
+    if (per_element_geo) {
+        if (nq == 12)
+            return {256, 512, false, f64 ? 320 : 0};
+        if (f64)
+            return nq == 3 || nq == 8 ? none
+                   : nq == 4          ? LinePick{64, 64}
+                   : nq < 6           ? LinePick{128, 128}
+                   : nq == 10         ? LinePick{256, 512}
+                                      : LinePick{256, 256, false, nq == 9 ? 640 : 0};
+        return nq == 2 || nq == 10 ? none
+               : nq < 5            ? LinePick{512, 256}
+               : nq == 5           ? LinePick{128, 128, true}
+               : nq == 6           ? LinePick{256, 128}
+               : nq == 8           ? LinePick{512, 256}
+                                   : LinePick{256, 256};
+    }
+    if (dirs == 3) {
+        if (f64)
+            return nq == 10              ? LinePick{256, 512, false, 384}
+                   : nf == 8 && nq == 3  ? LinePick{64, 64}
+                   : nf == 8 && nq == 5  ? LinePick{128, 128, true}
+                                         : none;
+        return nq == 6              ? LinePick{256, 256}
+               : nf == 8 && nq == 5 ? LinePick{128, 128, true}
+               : nf == 8 && nq == 9 ? LinePick{256, 768}
+                                    : none;
+    }
+    if (nq == 12)
+        return {256, 1024};
+    if (nf == 5)
+        return nq == 6          ? LinePick{256, 256}
+               : f64 && nq == 7 ? LinePick{256, 192, false, 1280}
+               : nq == 9        ? LinePick{256, f64 ? 512 : 256}
+                                : none;
+    return nq == 5           ? LinePick{128, 128, !f64}
+           : nq == 6         ? LinePick{256, 256}
+           : nq == 7         ? LinePick{256, 384}
+           : f64 && nq == 3  ? LinePick{64, 64}
+           : f64 && nq == 10 ? LinePick{256, 512}
+           : !f64 && nq == 9 ? LinePick{256, 768}
+                             : none;
+}
+
+// Whether the volume term of five fields, r+s+t, of Ne elements has a tile of
+// its own for the calls that name no tile shape (launch_volume_ext).
+template <typename T>
+constexpr bool volume_own_tile(int nq, int64_t Ne)
+{
+    const LinePick p = line_pick<T>(nq, 5, 7, false);
+    return use_slice<T>(nq) || (p.lanes > 0 && Ne > p.few);
+}
 
 // Workgroup cap of the strided k-slice and t-column launches set by
 // sem_set_max_workgroups (0 = none); one relaxed atomic load.

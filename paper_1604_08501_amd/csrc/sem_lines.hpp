@@ -225,4 +225,150 @@ __device__ __forceinline__ void line_pressure(T Th, bool has_ref, double thr, co
         Pressure<T>::eval_full(Th, has_ref, thr, ph, pflux, pfull);
 }
 
+// One workgroup's volume term: EPB elements from e0 (ne of them in the mesh),
+// NT lanes, RES = all directions staged at once (two barriers), or 1 at a time
+// (two barriers each).  A node's results are read and its next fluxes written
+// by the same lane, so the next direction needs no barrier of its own.
+template <typename T, int NQ, int EPB, int NF, int RES>
+constexpr int line_tile_values()
+{
+    return RES * EPB * NF * LineLds<T, NQ>::WORDS + pow_table_values<T>();
+}
+
+template <typename T, int NQ, int EPB, int NT, int RES, bool ACC, int NF, int DIRS, bool GEOE>
+__device__ __forceinline__ void line_tile(const BlockPtrs<T>& B, int64_t e0, int ne,
+                                          const Phys& phys, T* __restrict__ sF)
+{
+    using L = LineLds<T, NQ>;
+    constexpr int M = NQ * NQ * NQ;
+    constexpr int NPT = (EPB * M + NT - 1) / NT;
+    constexpr int ND = ndirs<DIRS>();
+    constexpr int NARR = EPB * NF;
+    constexpr int NW = NT / 64;
+    constexpr bool STREAM = Shape<NQ>::template stream_loads<T>();
+    static_assert(NT % 64 == 0 && (RES == ND || RES == 1), "whole waves; all directions or one");
+    const int tid = threadIdx.x;
+    const bool has_ref = B.theta_ref != nullptr;
+    LinePhys<T> ph;
+    static_cast<Phys&>(ph) = phys;
+    if constexpr (sizeof(T) == 8) {
+        constexpr int AT = RES * NARR * L::WORDS;
+        ph.tab = sF + AT;
+        stage_pow_tables<NT>(sF + AT);
+    }
+    auto ld = [](const auto* p) { return STREAM ? ld_stream(p) : *p; };
+    NodeState<T, NF> st[NPT];
+    double thr[NPT];
+    bool live[NPT];
+    int at[NPT];   // the node's word in the staged arrays
+#pragma unroll
+    for (int p = 0; p < NPT; ++p) {
+        const int t = tid + p * NT;
+        live[p] = t < EPB * M && t / M < ne;
+        at[p] = (t / M) * (NF * L::WORDS) + L::pos(t % NQ, (t / NQ) % NQ, (t / (NQ * NQ)) % NQ);
+        if (live[p]) {
+            const int64_t e = e0 + (EPB == 1 ? 0 : t / M);
+            const int m = EPB == 1 ? t : t % M;
+            const T* __restrict__ qe = B.q + e * (NF * M) + m;
+            st[p].rho = ld(qe);
+            st[p].U1 = ld(qe + M);
+            st[p].U2 = ld(qe + 2 * M);
+            st[p].U3 = ld(qe + 3 * M);
+            st[p].Th = ld(qe + 4 * M);
+#pragma unroll
+            for (int b = 5; b < NF; ++b)
+                st[p].Q[b - 5] = ld(qe + b * M);
+            const T* __restrict__ ge = GEOE ? B.geo + e * 10 : B.geo + e * (10 * M) + m;
+#pragma unroll
+            for (int s = 0; s < 9; ++s)
+                if ((DIRS >> (s / 3)) & 1)
+                    st[p].g[s] = GEOE ? ge[s] : ld(ge + s * M);
+            st[p].jinv = GEOE ? ge[9] : ld(ge + 9 * M);
+            st[p].src = (T)0;
+            thr[p] = 0.0;
+            if (has_ref) {
+                st[p].src = ld(B.rho_ref + e * M + m);
+                thr[p] = ld(B.theta_ref + e * M + m);
+            }
+        }
+    }
+    LineD<T, NQ> A;
+    A.load(B.D);
+    if constexpr (sizeof(T) == 8)
+        __syncthreads();   // the tables are staged
+    T acc[NPT][NF];
+#pragma unroll
+    for (int p = 0; p < NPT; ++p)
+        if (live[p]) {
+            NodeState<T, NF>& s = st[p];
+            s.src = -(T)ph.grav * (s.rho - s.src);
+            T pfull;
+            line_pressure<T>(s.Th, has_ref, thr[p], ph, s.pp, pfull);
+            s.rinv = recip(s.rho);
+            if constexpr (RES == ND)
+#pragma unroll
+                for (int d = 0; d < 3; ++d)
+                    if ((DIRS >> d) & 1)
+                        put_flux<T, L::WORDS, NF>(
+                            s, d, sF + dir_slot<DIRS>(d) * (NARR * L::WORDS) + at[p]);
+        }
+    if constexpr (RES == ND) {
+        __syncthreads();
+        if constexpr (DIRS & 1)
+            transform_lines<T, NQ, 0, NARR, NW>(A, sF, first_group<T, NQ, NARR, NW>(0));
+        if constexpr (DIRS & 2)
+            transform_lines<T, NQ, 1, NARR, NW>(A, sF + dir_slot<DIRS>(1) * (NARR * L::WORDS),
+                                             first_group<T, NQ, NARR, NW>(dir_slot<DIRS>(1)));
+        if constexpr (DIRS & 4)
+            transform_lines<T, NQ, 2, NARR, NW>(A, sF + dir_slot<DIRS>(2) * (NARR * L::WORDS),
+                                             first_group<T, NQ, NARR, NW>(dir_slot<DIRS>(2)));
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < NPT; ++p)
+            if (live[p])
+#pragma unroll
+                for (int b = 0; b < NF; ++b) {
+                    T a = sF[at[p] + b * L::WORDS];
+#pragma unroll
+                    for (int d = 1; d < ND; ++d)
+                        a += sF[d * (NARR * L::WORDS) + at[p] + b * L::WORDS];
+                    acc[p][b] = a;
+                }
+    } else {
+        auto pass = [&](auto dir) {
+            constexpr int d = decltype(dir)::value;
+            if constexpr ((DIRS >> d) & 1) {
+#pragma unroll
+                for (int p = 0; p < NPT; ++p)
+                    if (live[p])
+                        put_flux<T, L::WORDS, NF>(st[p], d, sF + at[p]);
+                __syncthreads();
+                transform_lines<T, NQ, d, NARR, NW>(A, sF, first_group<T, NQ, NARR, NW>(0));
+                __syncthreads();
+#pragma unroll
+                for (int p = 0; p < NPT; ++p)
+                    if (live[p])
+#pragma unroll
+                        for (int b = 0; b < NF; ++b) {
+                            const T v = sF[at[p] + b * L::WORDS];
+                            acc[p][b] = dir_slot<DIRS>(d) == 0 ? v : acc[p][b] + v;
+                        }
+            }
+        };
+        pass(std::integral_constant<int, 0>{});
+        pass(std::integral_constant<int, 1>{});
+        pass(std::integral_constant<int, 2>{});
+    }
+    const RkStage no_rk{0.0, 0.0, 0.0};
+    const RkNode<T, false> no_rn{};
+#pragma unroll
+    for (int p = 0; p < NPT; ++p)
+        if (live[p]) {
+            const int t = tid + p * NT;
+            store_node<T, M, NF, ACC, false, Shape<NQ>::template stream_stores<T>()>(
+                B, no_rk, e0 + (EPB == 1 ? 0 : t / M), EPB == 1 ? t : t % M, acc[p], st[p].jinv,
+                st[p].src, no_rn);
+        }
+}
+
 }  // namespace semk
