@@ -366,3 +366,39 @@ def test_rhs_on_both_sides_of_the_lane_rule(sv, oracle_mod, Nq, fp32, ne):
     w = I.warped_workload(N=Nq - 1, n_side=13, n_elements=ne, k=320 + Nq)
     e = err(host(run_rhs(sv, w, fp32=fp32)), oracle_vs(oracle_mod, w, fp32=fp32))
     assert e.max() <= (2e-5 if fp32 else 1e-12), e
+
+
+@pytest.mark.parametrize("Nq,ne", [(2, 7), (2, 9), (3, 1), (3, 5), (4, 3), (5, 2), (8, 1), (9, 2)])
+def test_surface_ragged_workgroups(sv, oracle_mod, Nq, ne):
+    """Workgroups whose last elements are missing, with boundary faces, and a
+    state that is not a number in one element: it reaches nothing that it does
+    not reach in the oracle."""
+    w = I.warped_workload(N=Nq - 1, n_side=4, n_elements=ne, k=340 + Nq)
+    for fp32, tol in ((False, TOL64), (True, TOL32)):
+        ref = oracle_s(oracle_mod, w, fp32=fp32)
+        base = np.random.default_rng(Nq).standard_normal(w.q.shape)
+        if fp32:
+            base = base.astype(np.float32)
+        assert err(host(run(sv, w, fp32=fp32)), ref).max() <= tol
+        out = dev(base.copy())
+        run(sv, w, out=out, accumulate=True, fp32=fp32)
+        assert err(host(out), base + ref).max() <= tol
+    w.q[0, 4, 0] = np.nan
+    bad = np.isnan(oracle_s(oracle_mod, w))
+    assert not np.isnan(host(run(sv, w)))[~bad].any()
+
+
+@pytest.mark.parametrize("Nq,fp32,ne", [(4, False, 15625), (4, False, 15627), (5, False, 8001),
+                                        (10, True, 2000), (10, True, 2001)])
+def test_surface_on_both_sides_of_the_size_rule(sv, oracle_mod, Nq, fp32, ne):
+    """Fields of 8 MB and just beyond: the mesh size at which the kernel (and
+    its loads) change.  The forward gates."""
+    w = I.warped_workload(N=Nq - 1, n_side=26, n_elements=ne, k=360 + Nq)
+    ref = oracle_s(oracle_mod, w, fp32=fp32)
+    tol = TOL32 if fp32 else TOL64
+    assert err(host(run(sv, w, fp32=fp32)), ref).max() <= tol
+    base = np.random.default_rng(Nq).standard_normal(w.q.shape).astype(
+        np.float32 if fp32 else np.float64)
+    out = dev(base.copy())
+    run(sv, w, out=out, accumulate=True, fp32=fp32)
+    assert err(host(out), base + ref).max() <= tol
