@@ -508,10 +508,25 @@ sem_status default_shapes(PlanCore& p)
 // FP64 (253), 2 to 5 236 (126) and 288 (286), 5, 7, 9 196 (151) and 602 (285).
 // They hold more elements per tile at Nq = 2, 3 and 5, though, so they stay
 // where only they fit the static call's tile table (a plan then takes them too,
-// for the same bits).
+// for the same bits).  FP64 plans up to Nq = 6-8 of few nodes, all of whose
+// tiles are resident at once, keep them as well: 256 lanes finish a tile
+// sooner than 512 (Nq = 4, 6, 8: 20, 170, 300, 600 elements each 7.8, 9.1, 11.3,
+// 22.5 us against 9.9, 10.8, 13.0, 19.8; 2, 4, 7: 20, 170, 300 7.7, 9.2, 11.1
+// against 8.7, 10.2, 10.5).
 int semapi::batch_default_shapes(sem_dtype dt, bool rk, const BatchOrder* orders, int n,
                                  DefaultTile* shapes)
 {
+    int top = 0;
+    int64_t nodes = 0;
+    for (int i = 0; i < n; ++i) {
+        top = std::max(top, orders[i].nq);
+        nodes += orders[i].elements * orders[i].nq * orders[i].nq * orders[i].nq;
+    }
+    if (dt == SEM_F64 && !rk && top >= 6 && top <= 8 && nodes <= 240000) {
+        const int dense = pick_shapes(dt, rk, true, orders, n, shapes);
+        if (dense && fits_static(orders, n, shapes))
+            return dense;
+    }
     const int nt = pick_shapes(dt, rk, false, orders, n, shapes);
     if (rk || (nt && fits_static(orders, n, shapes)))
         return nt;
