@@ -57,11 +57,12 @@ def flops_per_node(Nq: int) -> int:
 
 # Sources that define the kernels whose measured traffic is recorded (the
 # single-order volume and adjoint kernels, the extended kernels, the surface
-# kernel and the whole-rate kernel).
+# kernels and the whole-rate kernels).
 VOLUME_KERNEL_SOURCES = ("sem_device.hpp", "sem_internal.hpp", "kernels.inc", "kernels_f64.hip",
                          "kernels_f32.hip", "ext.inc", "ext_f64.hip", "ext_f32.hip",
                          "surface.inc", "surface_f64.hip", "surface_f32.hip", "rhs.inc",
-                         "rhs_f64.hip", "rhs_f32.hip")
+                         "rhs_f64.hip", "rhs_f32.hip", "sem_lines.hpp", "sem_slice.hpp",
+                         "slice_f64.hip", "sem_pow.hpp", "sem_pow_tables.inc")
 
 
 def kernel_source_hash() -> str:
