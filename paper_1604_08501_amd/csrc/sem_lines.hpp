@@ -230,9 +230,15 @@ __device__ __forceinline__ void line_pressure(T Th, bool has_ref, double thr, co
 // (two barriers each).  A node's results are read and its next fluxes written
 // by the same lane, so the next direction needs no barrier of its own.
 template <typename T, int NQ, int EPB, int NF, int RES>
+constexpr int line_tile_tables()
+{
+    return pow_tables_at(RES * EPB * NF * LineLds<T, NQ>::WORDS);
+}
+
+template <typename T, int NQ, int EPB, int NF, int RES>
 constexpr int line_tile_values()
 {
-    return RES * EPB * NF * LineLds<T, NQ>::WORDS + pow_table_values<T>();
+    return line_tile_tables<T, NQ, EPB, NF, RES>() + pow_table_values<T>();
 }
 
 template <typename T, int NQ, int EPB, int NT, int RES, bool ACC, int NF, int DIRS, bool GEOE>
@@ -252,9 +258,9 @@ __device__ __forceinline__ void line_tile(const BlockPtrs<T>& B, int64_t e0, int
     LinePhys<T> ph;
     static_cast<Phys&>(ph) = phys;
     if constexpr (sizeof(T) == 8) {
-        constexpr int AT = RES * NARR * L::WORDS;
-        ph.tab = sF + AT;
-        stage_pow_tables<NT>(sF + AT);
+        constexpr int TABLES = line_tile_tables<T, NQ, EPB, NF, RES>();
+        ph.tab = sF + TABLES;
+        stage_pow_tables<NT, TABLES>(sF);
     }
     auto ld = [](const auto* p) { return STREAM ? ld_stream(p) : *p; };
     NodeState<T, NF> st[NPT];

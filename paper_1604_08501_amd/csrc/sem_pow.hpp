@@ -30,10 +30,19 @@ struct PowPhys : Phys {
     const double* tab;
 };
 
-template <int NT>
-__device__ __forceinline__ void stage_pow_tables(double* __restrict__ tab)
+// Place of the tables behind n values of LDS: two values are written at a time.
+constexpr int pow_tables_at(int n)
 {
+    return (n + 1) & ~1;
+}
+
+// The tables to smem + AT (smem: 16-byte aligned), by NT lanes.
+template <int NT, int AT>
+__device__ __forceinline__ void stage_pow_tables(double* __restrict__ smem)
+{
+    static_assert(AT % 2 == 0, "the tables are written 16 bytes at a time");
     typedef double double2_t __attribute__((ext_vector_type(2)));
+    double* __restrict__ tab = smem + AT;
     for (int x = threadIdx.x; x < kPowTableValues / 2; x += NT)
         reinterpret_cast<double2_t*>(tab)[x] =
             reinterpret_cast<const double2_t*>(kPowTables)[x];

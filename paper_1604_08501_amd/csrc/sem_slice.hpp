@@ -136,14 +136,15 @@ __device__ __forceinline__ void slice_tile(const BlockPtrs<double>& B, const int
     using L = LineLds<double, 8>;
     constexpr int M = 512, N = 7;
     double* __restrict__ sF = smem;
-    double* __restrict__ sTab = smem + NF * L::WORDS;
+    constexpr int TABLES = NF * L::WORDS;
+    double* __restrict__ sTab = smem + TABLES;
     double* __restrict__ sD = sTab + kPowTableValues;
     double* __restrict__ sOwn = sD + 64;   // [face][value][64]
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = tid & 7, j = (tid >> 3) & 7, k = w;
     const bool has_ref = B.theta_ref != nullptr;
-    stage_pow_tables<512>(sTab);
+    stage_pow_tables<512, TABLES>(smem);
     if (w == 7)
         sD[tid & 63] = B.D[tid & 63];
 
