@@ -402,3 +402,35 @@ def test_surface_on_both_sides_of_the_size_rule(sv, oracle_mod, Nq, fp32, ne):
     out = dev(base.copy())
     run(sv, w, out=out, accumulate=True, fp32=fp32)
     assert err(host(out), base + ref).max() <= tol
+
+
+@pytest.mark.parametrize("Nq,ne", [(2, 17), (3, 5), (4, 1), (4, 3), (5, 1), (6, 2), (4, 2800),
+                                   (4, 2801), (5, 1500), (5, 1501)])
+def test_rhs_node_by_node_and_on_lines(sv, oracle_mod, Nq, ne):
+    """v + s contracts node by node at the lowest orders, and at some only up to
+    a number of elements; workgroups whose last elements are missing, boundary
+    faces all round the sub-mesh.  The forward gates."""
+    w = I.warped_workload(N=Nq - 1, n_side=15, n_elements=ne, k=380 + Nq)
+    base = np.random.default_rng(Nq).standard_normal(w.q.shape)
+    for fp32, tol in ((False, TOL64), (True, TOL32)):
+        ref = oracle_vs(oracle_mod, w, fp32=fp32)
+        assert err(host(run_rhs(sv, w, fp32=fp32)), ref).max() <= tol
+        b = base.astype(np.float32) if fp32 else base
+        out = dev(b.copy())
+        run_rhs(sv, w, out=out, accumulate=True, fp32=fp32)
+        assert err(host(out), b + ref).max() <= tol
+
+
+@pytest.mark.parametrize("Nq", [2, 3, 6])
+@pytest.mark.parametrize("theta", [0.0, -1.0, 1e-310, np.inf, np.nan])
+def test_rhs_special_pressures_stay_in_their_lines(sv, oracle_mod, Nq, theta):
+    """A state whose pressure is special in one element reaches nothing that it
+    does not reach in the oracle."""
+    w = I.warped_workload(N=Nq - 1, n_side=3, k=400 + Nq)
+    w.q[1, 4, Nq * Nq + 1] = theta
+    with np.errstate(all="ignore"):
+        ref = oracle_vs(oracle_mod, w)
+    out = host(run_rhs(sv, w))
+    ok = np.isfinite(ref)
+    assert np.isfinite(out[ok]).all()
+    assert err(np.where(ok, out, 0.0), np.where(ok, ref, 0.0)).max() <= TOL64
