@@ -258,8 +258,8 @@ extern "C" sem_status sem_volume_rhs_tiled(int32_t Ne, int32_t Nq, sem_dtype dty
     int lay = code == SEM_LAYOUT_DEFAULT ? -1 : internal_layout(code);
     // no shape asked for: the order's own tile where there is one
     const bool own = epb == 0 && lay < 0 &&
-                     (dtype == SEM_F64 ? semh::volume_own_tile<double>(Nq, Ne)
-                                       : semh::volume_own_tile<float>(Nq, Ne));
+                     (dtype == SEM_F64 ? semh::volume_own_tile<double>(Nq, Ne, accumulate != 0)
+                                       : semh::volume_own_tile<float>(Nq, Ne, accumulate != 0));
     if (epb == 0 && lay < 0) {
         epb = dft.epb;
         lay = dft.lay;

@@ -113,12 +113,12 @@ hipError_t launch_rhs_slice(const semk::BlockPtrs<T>& B, const int32_t* nbr, con
 // Volume tiles on line transforms (sem_lines.hpp): elements of up to `nodes`
 // nodes together per workgroup (at least one element), up to `lanes` lanes,
 // all directions' fluxes staged at once or one direction's at a time.  Up to
-// `few` elements, and at any number where lanes = 0, the tile that contracts
-// node by node stays.
+// `few` elements (`few_add` when adding to rhs), and at any number where lanes =
+// 0, the tile that contracts node by node stays.
 struct LinePick {
     int nodes, lanes;
     bool all = false;
-    int few = 0;
+    int few = 0, few_add = few;
 };
 
 // The faster of both tiles, and among the line tiles of 64-1024 lanes and
@@ -142,11 +142,33 @@ struct LinePick {
 //     87 -> 82, 85 -> 77, 95 -> 89, 98.9 -> 95.8, 103 -> 98
 //   eight fields, r+s, FP64, Nq = 3, 5, 10: 160 -> 149, 158 -> 145, 162 -> 154;
 //     FP32, Nq = 5, 6, 9: 81 -> 77, 75 -> 70, 85 -> 82
-// Few elements, of which a CU holds two or three: a tile of several nodes per
-// lane takes longer for one of them than the other tile (FP64, metric terms
-// per element: 512 elements of Nq = 9 15.3 us against 13.3, 256 of Nq = 12 17.8
-// against 16.8; five fields, r+s, 256 of Nq = 10 13.3 against 11.3; r+s+t, 1024
-// of Nq = 7 16.7 against 16.2).
+// Few elements, of which a CU holds two or three: the launch takes as long as a
+// workgroup or two, and line transforms are the longer chain (fluxes to lines
+// and back, a barrier on either side, in FP64 the power's tables before all of
+// it; several nodes per lane where lanes are fewer than nodes).  Captured
+// launches on the same arrays, us, node by node -> lines on either side of
+// `few`:
+//   per-element metric terms, FP64, Nq = 2: 1000 elements 4.4 -> 5.6, 127000
+//     25.6 -> 23.2; 5: 720 6.0 -> 6.9, 3000 12.2 -> 11.5; 6: 450 5.8 -> 6.6, 720
+//     8.1 -> 7.9; 7: 450 8.0 -> 9.4, 720 11.4 -> 10.8; 9: 512 13.3 -> 15.3; 12: 256
+//     16.8 -> 17.8
+//   FP32, Nq = 3: 1000 3.9 -> 5.4, 31000 13.5 -> 13.5, 50000 19.4 -> 17.9; 4: 1000
+//     3.8 -> 4.6, 12000 10.2 -> 9.3; 6: 450 4.3 -> 5.7, 1844 8.2 -> 7.5; 7: 175
+//     4.8 -> 5.1, 720 6.8 -> 6.5; 8: 720 6.4 -> 7.1, 4700 25.5 -> 25.0; 9: 175
+//     5.9 -> 7.0, 720 11.7 -> 10.6
+//   five fields, r+s, FP64, Nq = 10: 256 11.3 -> 13.3; FP32, Nq = 6: 281 3.8 -> 4.1,
+//     720 5.2 -> 4.7 (adding 6.0 -> 5.2, and 281 5.0 -> 4.5)
+//   five fields, r+s+t, FP64, Nq = 6: 1 4.7 -> 5.2, 2 5.8 -> 5.3; 7: 1024 16.2 -> 16.7
+//   eight fields, r+s, FP64, Nq = 3: 2951 6.3 -> 6.8, 4722 8.8 -> 8.1 (adding 4
+//     3.7 -> 5.0, 42 5.7 -> 5.2); 5: 1844 10.3 -> 10.9, 2951 16.6 -> 16.3 (adding
+//     175 7.2 -> 6.0)
+//   eight fields, r+s+t, FP64, Nq = 3: 2951 8.1 -> 8.4, 4722 10.7 -> 9.8 (adding 4
+//     4.1 -> 6.1, 42 6.8 -> 6.3); 5: 281 7.4 -> 8.2, 1152 12.2 -> 10.8 (adding 2
+//     5.5 -> 7.1, 42 8.3 -> 7.3); 6: 1 5.1 -> 6.2, 2 6.9 -> 6.4; 7: 175 6.8 -> 8.1,
+//     281 11.9 -> 10.9; FP32, Nq = 6: 1 3.7 -> 4.2, 4 4.5 -> 4.4
+// (Left as they are, since both signs alternate: FP64 Nq = 4 per-element terms,
+// 450 4.7 -> 4.4, 1844 5.5 -> 6.1, 4722 9.7 -> 8.2; FP64 Nq = 6 eight fields
+// r+s+t, 175 7.5 -> 7.0, 281 8.0 -> 8.7, 720 11.7 -> 10.5.)
 template <typename T>
 constexpr LinePick line_pick(int nq, int nf, int dirs, bool per_element_geo)
 {
@@ -159,24 +181,25 @@ constexpr LinePick line_pick(int nq, int nf, int dirs, bool per_element_geo)
             return {256, 512, false, f64 ? 320 : 0};
         if (f64)
             return nq == 3 || nq == 8 ? none
+                   : nq == 2          ? LinePick{128, 128, false, 80000}
                    : nq == 4          ? LinePick{64, 64}
-                   : nq < 6           ? LinePick{128, 128}
+                   : nq == 5          ? LinePick{128, 128, false, 2200}
                    : nq == 10         ? LinePick{256, 512}
-                                      : LinePick{256, 256, false, nq == 9 ? 640 : 0};
+                                      : LinePick{256, 256, false, nq == 9 ? 640 : 600};
         return nq == 2 || nq == 10 ? none
-               : nq < 5            ? LinePick{512, 256}
+               : nq < 5            ? LinePick{512, 256, false, nq == 3 ? 30000 : 9500}
                : nq == 5           ? LinePick{128, 128, true}
-               : nq == 6           ? LinePick{256, 128}
-               : nq == 8           ? LinePick{512, 256}
-                                   : LinePick{256, 256};
+               : nq == 6           ? LinePick{256, 128, false, 1200}
+               : nq == 8           ? LinePick{512, 256, false, 3500}
+                                   : LinePick{256, 256, false, nq == 7 ? 700 : 600};
     }
     if (dirs == 3) {
         if (f64)
             return nq == 10              ? LinePick{256, 512, false, 384}
-                   : nf == 8 && nq == 3  ? LinePick{64, 64}
-                   : nf == 8 && nq == 5  ? LinePick{128, 128, true}
+                   : nf == 8 && nq == 3  ? LinePick{64, 64, false, 3500, 12}
+                   : nf == 8 && nq == 5  ? LinePick{128, 128, true, 2200, 3}
                                          : none;
-        return nq == 6              ? LinePick{256, 256}
+        return nq == 6              ? LinePick{256, 256, false, nf == 5 ? 512 : 0, nf == 5 ? 2 : 0}
                : nf == 8 && nq == 5 ? LinePick{128, 128, true}
                : nf == 8 && nq == 9 ? LinePick{256, 768}
                                     : none;
@@ -184,26 +207,31 @@ constexpr LinePick line_pick(int nq, int nf, int dirs, bool per_element_geo)
     if (nq == 12)
         return {256, 1024};
     if (nf == 5)
-        return nq == 6          ? LinePick{256, 256}
+        return nq == 6          ? LinePick{256, 256, false, f64 ? 1 : 0}
                : f64 && nq == 7 ? LinePick{256, 192, false, 1280}
                : nq == 9        ? LinePick{256, f64 ? 512 : 256}
                                 : none;
-    return nq == 5           ? LinePick{128, 128, !f64}
-           : nq == 6         ? LinePick{256, 256}
-           : nq == 7         ? LinePick{256, 384}
-           : f64 && nq == 3  ? LinePick{64, 64}
+    return nq == 5           ? LinePick{128, 128, !f64, f64 ? 600 : 0, f64 ? 3 : 0}
+           : nq == 6         ? LinePick{256, 256, false, 1}
+           : nq == 7         ? LinePick{256, 384, false, f64 ? 256 : 0}
+           : f64 && nq == 3  ? LinePick{64, 64, false, 3500, 8}
            : f64 && nq == 10 ? LinePick{256, 512}
            : !f64 && nq == 9 ? LinePick{256, 768}
                              : none;
 }
 
+// Whether Ne elements take the picked line tile.
+constexpr bool takes_lines(const LinePick& p, int64_t Ne, bool accumulate)
+{
+    return p.lanes > 0 && Ne > (accumulate ? p.few_add : p.few);
+}
+
 // Whether the volume term of five fields, r+s+t, of Ne elements has a tile of
 // its own for the calls that name no tile shape (launch_volume_ext).
 template <typename T>
-constexpr bool volume_own_tile(int nq, int64_t Ne)
+constexpr bool volume_own_tile(int nq, int64_t Ne, bool accumulate)
 {
-    const LinePick p = line_pick<T>(nq, 5, 7, false);
-    return use_slice<T>(nq) || (p.lanes > 0 && Ne > p.few);
+    return use_slice<T>(nq) || takes_lines(line_pick<T>(nq, 5, 7, false), Ne, accumulate);
 }
 
 // Workgroup cap of the strided k-slice and t-column launches set by

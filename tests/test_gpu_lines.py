@@ -90,3 +90,33 @@ def test_special_pressures_stay_in_their_lines(sv, Nq, theta):
     ok = np.isfinite(b)
     scale = np.broadcast_to(np.where(ok, np.abs(b), 0.0).max(axis=(0, 2))[None, :, None], b.shape)
     assert np.all(np.abs(a[ok] - b[ok]) <= 1e-12 * scale[ok])
+
+
+@pytest.mark.parametrize("fp32,Nq,n_side,Ne", [
+    (False, 2, 44, 80000), (False, 2, 44, 80001), (False, 5, 14, 2200), (False, 5, 14, 2201),
+    (False, 6, 9, 600), (False, 6, 9, 601), (False, 7, 9, 600), (False, 7, 9, 601),
+    (True, 3, 32, 30000), (True, 3, 32, 30001), (True, 4, 22, 9500), (True, 4, 22, 9501),
+    (True, 6, 11, 1200), (True, 6, 11, 1201), (True, 7, 9, 700), (True, 7, 9, 701),
+    (True, 8, 16, 3500), (True, 8, 16, 3501), (True, 9, 9, 600), (True, 9, 9, 601)])
+def test_per_element_metric_terms_few_elements(sv, oracle_mod, fp32, Nq, n_side, Ne):
+    w = first(I.affine_workload(N=Nq - 1, n_side=n_side, k=560 + Nq, with_adjoint=False), Ne)
+    check(Call(sv.volume_rhs_affine, lambda w: I.element_geo(w.geo)),
+          lambda u: oracle_mod.volume_rhs(u.D, u.geo, u.q, u.rho_ref, u.theta_ref,
+                                          u.phys.as_tuple()), w, fp32)
+
+
+@pytest.mark.parametrize("fp32,Nq,nf,dirs,Ne", [
+    (False, 3, 8, 3, 12), (False, 3, 8, 3, 13), (False, 3, 8, 3, 3500), (False, 3, 8, 3, 3501),
+    (False, 5, 8, 3, 3), (False, 5, 8, 3, 4), (False, 5, 8, 3, 2200), (False, 5, 8, 3, 2201),
+    (False, 3, 8, 7, 8), (False, 3, 8, 7, 9), (False, 3, 8, 7, 3500), (False, 3, 8, 7, 3501),
+    (False, 5, 8, 7, 3), (False, 5, 8, 7, 4), (False, 5, 8, 7, 600), (False, 5, 8, 7, 601),
+    (False, 6, 8, 7, 1), (False, 6, 8, 7, 2), (False, 7, 8, 7, 256), (False, 7, 8, 7, 257),
+    (False, 6, 5, 7, 1), (False, 6, 5, 7, 2), (True, 6, 5, 3, 2), (True, 6, 5, 3, 3),
+    (True, 6, 5, 3, 512), (True, 6, 5, 3, 513), (True, 6, 8, 7, 1), (True, 6, 8, 7, 2)])
+def test_fields_and_directions_few_elements(sv, oracle_mod, fp32, Nq, nf, dirs, Ne):
+    w = I.warped_workload(N=Nq - 1, n_side=16, n_elements=Ne, k=580 + Nq)
+    if nf == 8:
+        w = I.add_tracers(w)
+    check(Call(lambda *a, **k: sv.volume_rhs_ext(*a, dirs=dirs, **k)),
+          lambda u: oracle_mod.volume_rhs_ext(u.D, u.geo, u.q, u.rho_ref, u.theta_ref,
+                                              u.phys.as_tuple(), dirs=dirs), w, fp32)
