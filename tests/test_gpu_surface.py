@@ -434,3 +434,26 @@ def test_rhs_special_pressures_stay_in_their_lines(sv, oracle_mod, Nq, theta):
     ok = np.isfinite(ref)
     assert np.isfinite(out[ok]).all()
     assert err(np.where(ok, out, 0.0), np.where(ok, ref, 0.0)).max() <= TOL64
+
+
+@pytest.mark.parametrize("Nq,fp32,ne", [
+    (2, False, 801), (3, False, 1401), (4, False, 1251), (2, True, 1401), (3, True, 2301),
+    (4, True, 2501), (4, True, 31251), (5, False, 14001), (6, False, 8102), (7, False, 5103),
+    (8, False, 1954), (5, True, 28001), (6, True, 16204), (7, True, 10205), (8, True, 3907),
+    (9, True, 2744)])
+def test_surface_lane_per_node(sv, oracle_mod, Nq, fp32, ne):
+    """The kernel with a lane per node at the first size that takes it, every
+    order and precision that has it: ragged last workgroups, boundary faces, and
+    a state that is not a number in the last element.  The forward gates."""
+    w = I.warped_workload(N=Nq - 1, n_side=32, n_elements=ne, k=420 + Nq)
+    ref = oracle_s(oracle_mod, w, fp32=fp32)
+    tol = TOL32 if fp32 else TOL64
+    assert err(host(run(sv, w, fp32=fp32)), ref).max() <= tol
+    base = np.random.default_rng(Nq).standard_normal(w.q.shape).astype(
+        np.float32 if fp32 else np.float64)
+    out = dev(base.copy())
+    run(sv, w, out=out, accumulate=True, fp32=fp32)
+    assert err(host(out), base + ref).max() <= tol
+    w.q[-1, 4, 0] = np.nan
+    bad = np.isnan(oracle_s(oracle_mod, w, fp32=fp32))
+    assert not np.isnan(host(run(sv, w, fp32=fp32)))[~bad].any()
