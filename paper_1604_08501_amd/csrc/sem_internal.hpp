@@ -29,7 +29,7 @@ namespace semh {
 
 // A dispatch's work-item count (workgroups x lanes) is a 32-bit field of the
 // dispatch packet: launches beyond it fail with this error instead.
-inline bool dispatch_fits(int64_t groups, int threads)
+constexpr bool dispatch_fits(int64_t groups, int threads)
 {
     return groups >= 1 && groups * (int64_t)threads <= (int64_t)UINT32_MAX;
 }
@@ -220,10 +220,30 @@ constexpr LinePick line_pick(int nq, int nf, int dirs, bool per_element_geo)
                              : none;
 }
 
-// Whether Ne elements take the picked line tile.
-constexpr bool takes_lines(const LinePick& p, int64_t Ne, bool accumulate)
+// Elements and lanes of a picked tile's workgroup.
+constexpr int line_elements(const LinePick& p, int nq)
 {
-    return p.lanes > 0 && Ne > (accumulate ? p.few_add : p.few);
+    int e = 1;
+    while (2 * e * nq * nq * nq <= p.nodes)
+        e *= 2;
+    return e;
+}
+constexpr int line_lanes(const LinePick& p, int nq)
+{
+    const int lanes = (line_elements(p, nq) * nq * nq * nq + 63) / 64 * 64;
+    return lanes < p.lanes ? lanes : p.lanes;
+}
+
+// Whether Ne elements take the picked line tile.  It may need more lanes per
+// element than the other one, which then takes the largest launches (Nq = 6,
+// 256 lanes instead of 224 or, FP32 volume term, 128: 2^24 elements and more,
+// which FP32 arrays and per-element FP64 metric terms can still hold).
+constexpr bool takes_lines(const LinePick& p, int nq, int64_t Ne, bool accumulate)
+{
+    if (p.lanes == 0 || Ne <= (accumulate ? p.few_add : p.few))
+        return false;
+    const int per = line_elements(p, nq);
+    return dispatch_fits((Ne + per - 1) / per, line_lanes(p, nq));
 }
 
 // Whether the volume term of five fields, r+s+t, of Ne elements has a tile of
@@ -231,7 +251,7 @@ constexpr bool takes_lines(const LinePick& p, int64_t Ne, bool accumulate)
 template <typename T>
 constexpr bool volume_own_tile(int nq, int64_t Ne, bool accumulate)
 {
-    return use_slice<T>(nq) || takes_lines(line_pick<T>(nq, 5, 7, false), Ne, accumulate);
+    return use_slice<T>(nq) || takes_lines(line_pick<T>(nq, 5, 7, false), nq, Ne, accumulate);
 }
 
 // Workgroup cap of the strided k-slice and t-column launches set by

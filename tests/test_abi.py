@@ -471,3 +471,32 @@ def test_batch_rhs_static_keeps_its_element_limit(L, sv, dtype, Nq, epb):
             assert b"static tile table" in L.sem_last_error()
         elif not torch.cuda.is_available():
             assert L.sem_batch_rhs_static(block, 1, dtype, ctypes.byref(ph), None) == -3
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the arrays exist on paper only")
+@pytest.mark.parametrize("call,dtype,Nq,limit", [
+    ("volume", 1, 6, 33554428), ("ext5_rs", 1, 6, 19173960), ("affine", 0, 6, 19173960),
+    ("rhs", 1, 6, 19173960), ("surface", 1, 7, 16777215)])
+def test_launches_keep_their_element_limits(L, sv, call, dtype, Nq, limit):
+    """A launch holds 2^32 work-items, so a tile of fewer lanes per element takes
+    more elements.  The limit of each call that a tile of more lanes could lower
+    below what FP32 arrays (or per-element FP64 metric terms) of 288 GiB hold:
+    `limit` elements reach the device (there is none here), far more do not."""
+    ph = ctypes.byref(sv.sem_phys(1e5, 1.4, 287.0, 9.81))
+    D, geo, q, out, nbr = (k << 44 for k in (1, 2, 3, 4, 5))
+
+    def run(Ne):
+        if call == "volume":
+            return L.sem_volume_rhs(Ne, Nq, dtype, D, geo, q, None, None, ph, out, 0, None)
+        if call == "ext5_rs":
+            return L.sem_volume_rhs_ext(Ne, Nq, dtype, 5, 3, D, geo, q, None, None, ph, out, 0,
+                                        None)
+        if call == "affine":
+            return L.sem_volume_rhs_affine(Ne, Nq, dtype, D, geo, q, None, None, ph, out, 0, None)
+        if call == "rhs":
+            return L.sem_rhs(Ne, Nq, dtype, D, geo, q, None, None, nbr, ph, out, 0, None)
+        return L.sem_surface_rhs(Ne, Nq, dtype, nbr, geo, q, None, ph, out, 0, None)
+    assert run(limit) == -3
+    assert b"invalid configuration" not in L.sem_last_error()
+    assert run(2 * limit + 16) == -3
+    assert b"invalid configuration" in L.sem_last_error()

@@ -28,7 +28,7 @@ CHECK(2) CHECK(3) CHECK(4) CHECK(5) CHECK(6) CHECK(7) CHECK(8) CHECK(9) CHECK(10
 
 @pytest.mark.parametrize("inc,at", [
     ("rhs.inc", "semk::RhsShape<double, NQ>::TABLES"),
-    ("rhs.inc", "semk::RhsShape<double, NQ, true>::TABLES"),
+    ("rhs.inc", "semk::RhsShape<double, NQ, semk::FEW>::TABLES"),
     ("surface.inc", "semk::SurfShape<double, NQ>::TABLES"),
     ("sem_lines.hpp", "semk::line_tile_tables<double, NQ, 1, 5, 1>()"),
     ("sem_lines.hpp", "semk::line_tile_tables<double, NQ, 1, 8, 3>()"),
