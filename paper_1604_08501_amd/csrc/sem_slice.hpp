@@ -235,7 +235,7 @@ __device__ __forceinline__ void slice_tile(const BlockPtrs<double>& B, const int
         if (en >= 0) {
             double pfull;
             table_pressure(nq[4], has_ref, nth, ph, np, pfull);
-            nc = root(ph.gamma * pfull * recip(nq[0]));
+            nc = root(ph.gamma * pfull / nq[0]);
         }
     }
     if constexpr (DIRS & 4) {
