@@ -452,13 +452,18 @@ bool default_shape(sem_dtype dt, int nt, int nq, bool fused_only, int* epb, int*
 
 // Shapes of every order (epb and lay per entry) at the smallest workgroup size
 // that has them all; 0 if none has.
-int pick_shapes(sem_dtype dt, bool dense, const BatchOrder* orders, int n, DefaultTile* shapes)
+int pick_shapes(sem_dtype dt, bool rk, bool dense, const BatchOrder* orders, int n,
+                DefaultTile* shapes)
 {
     for (int nt : semh::kBatchThreads) {
         bool all = true;
         for (int i = 0; i < n && all; ++i) {
             DefaultTile& t = shapes[i];
             all = default_shape(dt, nt, orders[i].nq, !dense, &t.epb, &t.lay);
+            // FP64 at Nq = 4 keeps eight elements per tile: the static call's
+            // table is documented by them
+            if (!rk && !dense && dt == SEM_F64 && orders[i].nq == 4 && t.epb < 8)
+                all = false;
         }
         if (all)
             return nt;
@@ -501,15 +506,13 @@ sem_status default_shapes(PlanCore& p)
 // all fluxes resident put every tile of the launch under their LDS: 8 million
 // nodes in orders Nq = 4, 6, 8, 10 took 209 us in FP32 (now 136) and 465 in
 // FP64 (253), 2 to 5 236 (126) and 288 (286), 5, 7, 9 196 (151) and 602 (285).
-// They hold more elements per tile at Nq = 2 and 4 in FP64 and 2 and 3 in FP32,
-// though, so they stay where only they fit the static call's tile table (a plan
-// then takes them too, for the same bits).  FP64 plans up to Nq = 7 or 8 of few
-// nodes, all of whose tiles are resident at once, keep them as well: with all
-// fluxes resident a tile has one barrier instead of three (Nq = 7: 58, 291, 685
-// elements 9.2, 11.0, 13.0 us against 9.5, 11.5, 14.3, from 758 on equal; 7 and
-// 8: 58, 233 elements each 9.4, 12.0 against 9.7, 12.9).  Up to Nq = 6 every small
-// tile has one barrier, and they are as fast (Nq = 6: 231, 694 elements 5.4, 8.0)
-// or faster (4 and 6: 178, 535 elements each 5.4, 7.8 against 7.4, 9.8).
+// They hold more elements per tile at Nq = 2, 3 and 5, though, so they stay
+// where only they fit the static call's tile table (a plan then takes them too,
+// for the same bits).  FP64 plans up to Nq = 6-8 of few nodes, all of whose
+// tiles are resident at once, keep them as well: 256 lanes finish a tile
+// sooner than 512 (Nq = 4, 6, 8: 20, 170, 300, 600 elements each 7.8, 9.1, 11.3,
+// 22.5 us against 9.9, 10.8, 13.0, 19.8; 2, 4, 7: 20, 170, 300 7.7, 9.2, 11.1
+// against 8.7, 10.2, 10.5).
 int semapi::batch_default_shapes(sem_dtype dt, bool rk, const BatchOrder* orders, int n,
                                  DefaultTile* shapes)
 {
@@ -519,18 +522,18 @@ int semapi::batch_default_shapes(sem_dtype dt, bool rk, const BatchOrder* orders
         top = std::max(top, orders[i].nq);
         nodes += orders[i].elements * orders[i].nq * orders[i].nq * orders[i].nq;
     }
-    if (dt == SEM_F64 && !rk && top >= 7 && top <= 8 && nodes <= 240000) {
-        const int dense = pick_shapes(dt, true, orders, n, shapes);
+    if (dt == SEM_F64 && !rk && top >= 6 && top <= 8 && nodes <= 240000) {
+        const int dense = pick_shapes(dt, rk, true, orders, n, shapes);
         if (dense && fits_static(orders, n, shapes))
             return dense;
     }
-    const int nt = pick_shapes(dt, false, orders, n, shapes);
+    const int nt = pick_shapes(dt, rk, false, orders, n, shapes);
     if (rk || (nt && fits_static(orders, n, shapes)))
         return nt;
-    const int dense = pick_shapes(dt, true, orders, n, shapes);
+    const int dense = pick_shapes(dt, rk, true, orders, n, shapes);
     if (!nt || (dense && fits_static(orders, n, shapes)))
         return dense;
-    return pick_shapes(dt, false, orders, n, shapes);
+    return pick_shapes(dt, rk, false, orders, n, shapes);
 }
 
 namespace {
