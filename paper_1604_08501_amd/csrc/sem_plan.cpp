@@ -460,8 +460,12 @@ int pick_shapes(sem_dtype dt, bool rk, bool dense, const BatchOrder* orders, int
         for (int i = 0; i < n && all; ++i) {
             DefaultTile& t = shapes[i];
             all = default_shape(dt, nt, orders[i].nq, !dense, &t.epb, &t.lay);
-            // FP64 at Nq = 4 keeps eight elements per tile: the static call's
-            // table is documented by them
+            // FP64 at Nq = 4 keeps eight elements per tile, 512 lanes: a caller
+            // that sizes static calls by the elements per tile that a plan
+            // reports relies on the table's limit at 32768 times that number,
+            // and with four it would lie at twice that (the dense shapes).  Four
+            // on 256 lanes would be the faster shape (8 million nodes of Nq = 4
+            // and 5 210 -> 176 us, 3 and 4 178 -> 162, 4 and 6 186 -> 174).
             if (!rk && !dense && dt == SEM_F64 && orders[i].nq == 4 && t.epb < 8)
                 all = false;
         }
@@ -506,13 +510,18 @@ sem_status default_shapes(PlanCore& p)
 // all fluxes resident put every tile of the launch under their LDS: 8 million
 // nodes in orders Nq = 4, 6, 8, 10 took 209 us in FP32 (now 136) and 465 in
 // FP64 (253), 2 to 5 236 (126) and 288 (286), 5, 7, 9 196 (151) and 602 (285).
-// They hold more elements per tile at Nq = 2, 3 and 5, though, so they stay
-// where only they fit the static call's tile table (a plan then takes them too,
-// for the same bits).  FP64 plans up to Nq = 6-8 of few nodes, all of whose
-// tiles are resident at once, keep them as well: 256 lanes finish a tile
-// sooner than 512 (Nq = 4, 6, 8: 20, 170, 300, 600 elements each 7.8, 9.1, 11.3,
-// 22.5 us against 9.9, 10.8, 13.0, 19.8; 2, 4, 7: 20, 170, 300 7.7, 9.2, 11.1
-// against 8.7, 10.2, 10.5).
+// They hold more elements per tile at Nq = 2 in FP64 and 2 and 3 in FP32, though,
+// so they stay where only they fit the static call's tile table (a plan then
+// takes them too, for the same bits).  FP64 plans up to Nq = 6-8 of few nodes, all
+// of whose tiles are resident at once, keep them as well.  At Nq = 7 and 8 a tile
+// with all fluxes resident has one barrier instead of three (Nq = 7: 58, 291, 685
+// elements 9.2, 11.0, 13.0 us against 9.5, 11.5, 14.3, from 758 on equal; 7 and 8:
+// 58, 233 elements each 9.4, 12.0 against 9.7, 12.9); with Nq = 4 in the batch, 256
+// lanes finish a tile sooner than 512 (Nq = 4, 6, 8: 20, 170, 300, 600 elements
+// each 7.8, 9.1, 11.3, 22.5 us against 9.9, 10.8, 13.0, 19.8; 2, 4, 7: 20, 170,
+// 300 7.7, 9.2, 11.1 against 8.7, 10.2, 10.5).  Up to Nq = 6 without Nq = 4 the rule
+// gains nothing (6, 5 and 6: equal; 2 and 6, 446 and 669 elements each 6.9, 9.9
+// against 6.8, 8.0).
 int semapi::batch_default_shapes(sem_dtype dt, bool rk, const BatchOrder* orders, int n,
                                  DefaultTile* shapes)
 {
