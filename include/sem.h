@@ -89,11 +89,22 @@ typedef struct sem_phys {
 /* Tile shape of the single-order kernels: elements per workgroup and LDS
  * layout.  SEM_LAYOUT_FULL stages the contravariant fluxes of all three
  * reference directions in LDS (one barrier); SEM_LAYOUT_ALIAS stages one
- * direction at a time (a third of the LDS, three barriers).  Zeros select the
- * built-in default for (dtype, Nq), the fastest compiled shape measured on
- * MI355X; a zero element count with an explicit layout takes the default's
- * count when that shape exists (else the smallest compiled one), and an
- * explicit count with SEM_LAYOUT_DEFAULT takes FULL if compiled, else ALIAS. */
+ * direction at a time (a third of the LDS, three barriers).  A zero element
+ * count with an explicit layout takes the built-in shape's count when that
+ * shape exists (else the smallest compiled one), and an explicit count with
+ * SEM_LAYOUT_DEFAULT takes FULL if compiled, else ALIAS.
+ *
+ * Zeros, or no sem_tile, leave the choice to the library, which takes the
+ * tile that measured fastest on MI355X for the call's dtype, Nq, Ne and
+ * accumulate.  At some orders that is a tile of another kind, which
+ * sem_tile_options does not list and no sem_tile names.  The same holds for
+ * every entry point below without a sem_tile.  All tiles compute the same
+ * values up to rounding (the order of additions, and in FP64 one of two forms
+ * of x^gamma, each within 3 units of 2^-53 for an atmosphere's pressures), so
+ * an element's last bits can depend on how many elements share its call; for
+ * equal arguments they do not change from call to call.  A caller that needs
+ * the same bits from parts of a mesh as from the whole names a shape
+ * (sem_volume_rhs_tiled). */
 #define SEM_LAYOUT_DEFAULT 0
 #define SEM_LAYOUT_FULL 1
 #define SEM_LAYOUT_ALIAS 2
@@ -129,7 +140,7 @@ sem_status sem_volume_rhs(int32_t Ne, int32_t Nq, sem_dtype dtype,
                           const sem_phys* phys, void* rhs, int32_t accumulate,
                           void* stream);
 
-/* As sem_volume_rhs, with an explicit tile shape (NULL = default).  A shape
+/* As sem_volume_rhs, with an explicit tile shape (NULL = the library's choice).  A shape
  * that is not compiled for (dtype, Nq) returns SEM_ERR_UNSUPPORTED, an
  * unknown layout code SEM_ERR_INVALID_ARG.  Every shape computes the same
  * values (up to the order of floating-point additions). */
@@ -162,7 +173,7 @@ int32_t sem_tile_options(sem_dtype dtype, int32_t Nq, sem_tile* out, int32_t cap
  *             geo slots of an excluded direction are not read
  *   Nq        2..10, 12 or 16
  * All other arguments, the gravity source and the reference state are as for
- * sem_volume_rhs.  Each (Nq, nfields, dirs) has one built-in tile shape; r+s at
+ * sem_volume_rhs.  The library chooses the tile (see sem_tile); r+s at
  * Nq >= 12 tiles each element by groups of k-slices.  r+s+t at Nq = 16 is two
  * launches on `stream`: the r+s term with the source (as requested, overwrite
  * or accumulate), then the t term added to it; the result is the same up to

@@ -607,13 +607,13 @@ __device__ __forceinline__ void contract_r_lanes(const T* __restrict__ sD, const
 }
 
 // ---------------------------------------------------------------------------
-// Surface term of dq/dt = v + s fused into the forward tile's epilogue (the
-// strong-form discontinuous Galerkin face term with a local Lax-Friedrichs
-// flux; see the surface kernel for the formula).  Faces f = 2 d + side of an
-// element; a face node is named by its indices (a2, b2) along the face's two
-// tangential directions (for d = r: s, t; for s: r, t; for t: r, s), and
-// meets the node with the same tangential indices at the other end of
-// direction d in the element across the face.
+// Parts of the surface term of dq/dt = v + s that the surface kernels and the
+// tiles of v + s share (the strong-form discontinuous Galerkin face term with a
+// local Lax-Friedrichs flux; see the surface kernel for the formula).  An
+// element has faces f = 2 d + side; a face node is named by its indices (a2, b2)
+// along the face's two tangential directions (for d = r: s, t; for s: r, t; for
+// t: r, s), and meets the node with the same tangential indices at the other end
+// of direction d in the element across the face.
 // ---------------------------------------------------------------------------
 
 // Workgroup index whose elements this workgroup handles: hardware workgroup

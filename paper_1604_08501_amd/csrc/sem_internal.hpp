@@ -123,7 +123,7 @@ struct LinePick {
 
 // The faster of both tiles, and among the line tiles of 64-1024 lanes and
 // nodes, on 3.5 million nodes (per-element metric terms and five fields r+s+t
-// up to Nq = 10: 8 million), where it gained 3% or more.  The line tile wins
+// up to Nq = 10: 8 million), where it gained some 3% or more.  The line tile wins
 // where the other one is held by its LDS reads or its few workgroups per CU:
 // orders that are no power of two, eight fields, metric terms that cost no
 // bandwidth.  us, node by node -> lines:

@@ -25,8 +25,16 @@ typedef float float4_t __attribute__((ext_vector_type(4)));
 //   32 lanes (64 banks) and writes in groups of 16 (32 banks).  In node order
 //   the r lines' writes take eight times as long.
 //   FP64, otherwise: node order.
-//   FP32: rows padded to an odd length, so that lanes on consecutive rows
-//   (the r lines) start in different banks.
+//   FP32: rows padded to an odd length, so that lanes on consecutive rows (the
+//   r lines) start in different banks, and at Nq = 8 those of the s lines too.
+//   64 lanes on consecutive nodes then span more than the 64 banks, so accesses
+//   in node order and of the t lines take twice their cycles at Nq = 6 and 8 (the
+//   s lines at 6 and 9): most of the conflict cycles that the counters show for
+//   the FP32 line and v + s tiles.  Unpadded, the r lines of Nq = 8 would take
+//   eight times theirs.
+// The v + s and surface tiles also conflict where boundary nodes stage and
+// gather face values: at Nq = 8 the nodes of faces r- and r+ (s- and s+) at the
+// same place of either face lie in the same banks, two lanes to each.
 template <typename T, int NQ>
 struct LineLds {
     static constexpr bool XOR = sizeof(T) == 8 && NQ == 8;

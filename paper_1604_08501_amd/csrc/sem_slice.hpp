@@ -5,11 +5,12 @@
 // through LDS without a workgroup barrier, one after the other through the
 // slice's share of the flux buffer, which then takes the t fluxes: 20 KB of
 // staged fluxes instead of 41 to 61, and no node state held across a barrier
-// (53 to 65 registers for the volume term instead of 101 and more).  What
-// that buys is occupancy: these kernels wait on HBM latency, VALU, LDS and
-// matrix units each well under their limits, so their time is set by how many
-// workgroups a CU holds.  The volume term runs four workgroups (32 waves) per
-// CU and v + s three; see the kernels for what each measured.
+// (55 to 64 registers for the volume term of five fields, 64 to 76 for eight and
+// 78 for v + s, instead of 101 and more).  What that buys is occupancy: these
+// kernels wait on HBM latency, VALU, LDS and matrix units each well under their
+// limits, so their time is set by how many workgroups a CU holds.  Five fields
+// run four workgroups (32 waves) per CU, eight fields and v + s three; see the
+// kernels for what each measured.
 #pragma once
 #include "sem_lines.hpp"
 #include "sem_pow.hpp"
@@ -30,7 +31,10 @@ __device__ __forceinline__ void wave_fence()
 // word in them.  The 16 columns of the matrix product are the slice's eight
 // lines twice, for the two halves of the rows: rows 4 h + kk along r, 2 kk + h
 // along s (h is bit 3 of the lane, kk the lane's sixteenth), so that a
-// 16-lane write touches every bank once in either direction.
+// 16-lane write touches every bank once in either direction.  (D's rows of 64
+// bytes do not: the operand loads here and in transform_t_lines, two of 24 and
+// two of 8 extra cycles per wave, are the volume tile's only bank conflicts, 64
+// cycles beside some 150 of LDS work.)
 template <int DIR, int NF, bool FIRST>
 __device__ __forceinline__ void contract_slice(const double* __restrict__ sD,
                                                const double (&f)[NF], int at, int k,

@@ -10,9 +10,10 @@ namespace semk {
 // four workgroups (32 waves) share a CU; eight fields need 78 registers, and
 // at 64 they spill (0.194 instead of 0.153 ms on the 6912-element shape).
 // Against the aliased tile of two elements, two nodes per lane (16 waves per
-// CU): 32768 elements 475 -> 457 us (6.4 TB/s), 3906 elements 63.9 -> 58.0 us;
-// per-element metric terms 358 -> 300 us (5.4 TB/s; the other arrays stream
-// at 6.3 TB/s in 257 us); 8 fields r+s+t 158 -> 153 us.
+// CU): 32768 elements 473 -> 468 us (6.3 TB/s, the rate of HBM), 4722 elements on
+// cached arrays 74.9 -> 67.7, 450 11.1 -> 9.2, 64 8.8 -> 5.6; per-element metric
+// terms, 32768 elements, 350 -> 296 us (5.5 TB/s; the other arrays stream at 6.3
+// TB/s in 257 us); 8 fields r+s+t 158 -> 153 us.
 template <int NF, int DIRS, bool GEOE, bool ACC>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512),
                           amdgpu_waves_per_eu(NF == 5 ? 8 : 6))) void
@@ -25,7 +26,7 @@ volume_slice_kernel(BlockPtrs<double> B, Phys ph)
 // v + s on 32768 elements: 732 us in the aliased tile (two workgroups per CU,
 // 76 KB of LDS), 580 us here with three (78 registers, 53,760 bytes of LDS,
 // the most that lets three share a CU), 662 us with two.  Above the volume
-// term's 457 us: the neighbours' face values (64 separate 64-byte pieces per
+// term's 468 us: the neighbours' face values (64 separate 64-byte pieces per
 // value on an r face: 26 us) and the longer chain of each element's phases.
 template <bool ACC>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(6))) void

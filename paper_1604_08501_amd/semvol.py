@@ -154,7 +154,7 @@ def _phys(phys) -> sem_phys:
 
 # The checks run on every call, and below some 10^5 nodes a call takes as long
 # as its host work, so they compare what the tensor hands out as it is: per
-# call on 64 elements of Nq = 5, 12.4 us before and 7.3 us now, of which the
+# call on 64 elements of Nq = 5, 12.4 us before and 8.0 us now, of which the
 # library's part is 4.1.
 _Tensor = torch.Tensor
 
@@ -199,8 +199,9 @@ def volume_rhs(q, geo, D, rho_ref=None, theta_ref=None, phys=None, out=None, acc
                elems_per_block: int = 0, layout: str = "default", stream=None) -> torch.Tensor:
     """Volume term of Eq. (volterm) plus the gravity source (``rhs = v(q)``,
     or ``out += v(q)`` with ``accumulate``).  ``elems_per_block``/``layout``
-    pick a compiled tile shape (see :func:`tile_options`); every shape
-    computes the same values."""
+    pick a compiled tile shape (see :func:`tile_options`); without them the
+    library chooses a tile by dtype, order and number of elements.  Every tile
+    computes the same values up to rounding."""
     Ne, Nq = _shape(q, D)
     M = Nq ** 3
     dt = q.dtype
