@@ -149,8 +149,8 @@ struct LinePick {
 // launches on the same arrays, us, node by node -> lines on either side of
 // `few`:
 //   per-element metric terms, FP64, Nq = 2: 1000 elements 4.4 -> 5.6, 127000
-//     25.6 -> 23.2; 5: 720 6.0 -> 6.9, 3000 12.2 -> 11.5; 6: 450 5.8 -> 6.6, 720
-//     8.1 -> 7.9; 7: 450 8.0 -> 9.4, 720 11.4 -> 10.8; 9: 512 13.3 -> 15.3; 12: 256
+//     25.6 -> 23.2; 5: 720 6.0 -> 6.9, 3000 12.2 -> 11.5; 6: 990
+//     7.9 -> 8.7, 1152 10.5 -> 9.7; 7: 450 8.0 -> 9.4, 720 11.4 -> 10.8; 9: 512 13.3 -> 15.3; 12: 256
 //     16.8 -> 17.8
 //   FP32, Nq = 3: 1000 3.9 -> 5.4, 31000 13.5 -> 13.5, 50000 19.4 -> 17.9; 4: 1000
 //     3.8 -> 4.6, 12000 10.2 -> 9.3; 6: 450 4.3 -> 5.7, 1844 8.2 -> 7.5; 7: 175
@@ -185,7 +185,7 @@ constexpr LinePick line_pick(int nq, int nf, int dirs, bool per_element_geo)
                    : nq == 4          ? LinePick{64, 64}
                    : nq == 5          ? LinePick{128, 128, false, 2200}
                    : nq == 10         ? LinePick{256, 512}
-                                      : LinePick{256, 256, false, nq == 9 ? 640 : 600};
+                                      : LinePick{256, 256, false, nq == 9 ? 640 : nq == 6 ? 1024 : 600};
         return nq == 2 || nq == 10 ? none
                : nq < 5            ? LinePick{512, 256, false, nq == 3 ? 30000 : 9500}
                : nq == 5           ? LinePick{128, 128, true}

@@ -94,7 +94,7 @@ def test_special_pressures_stay_in_their_lines(sv, Nq, theta):
 
 @pytest.mark.parametrize("fp32,Nq,n_side,Ne", [
     (False, 2, 44, 80000), (False, 2, 44, 80001), (False, 5, 14, 2200), (False, 5, 14, 2201),
-    (False, 6, 9, 600), (False, 6, 9, 601), (False, 7, 9, 600), (False, 7, 9, 601),
+    (False, 6, 11, 1024), (False, 6, 11, 1025), (False, 7, 9, 600), (False, 7, 9, 601),
     (True, 3, 32, 30000), (True, 3, 32, 30001), (True, 4, 22, 9500), (True, 4, 22, 9501),
     (True, 6, 11, 1200), (True, 6, 11, 1201), (True, 7, 9, 700), (True, 7, 9, 701),
     (True, 8, 16, 3500), (True, 8, 16, 3501), (True, 9, 9, 600), (True, 9, 9, 601)])
